@@ -170,6 +170,30 @@ __device__ __forceinline__ u32x4 buf_chunk(rsrc_t r, uint32_t voff, uint32_t sof
   return v;
 }
 
+// 16 bytes from an address of any alignment (one global_load_dwordx4).
+__device__ __forceinline__ u32x4 load16_any(const char* p) {
+  u32x4 v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
+}
+
+// Elements [0, n) of the 16-byte chunk at p, n below a chunk's count; the
+// others are zero and not read.
+template <int DT>
+__device__ __forceinline__ u32x4 load16_part(const char* p, int n) {
+  u32x4 v = {0u, 0u, 0u, 0u};
+  if constexpr (DT == DT_BF16) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (e < n) v[e >> 1] |= (uint32_t)((const uint16_t*)p)[e] << ((e & 1) * 16);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < n) v[e] = ((const uint32_t*)p)[e];
+  }
+  return v;
+}
+
 // Chunk loaders: 16 bytes = 8 bf16 or 4 fp32 starting at element `col` of a
 // row. Elements at or past `ncol` read as zero.
 template <int DT>

@@ -211,17 +211,25 @@ __device__ __forceinline__ void stage_mfma_fp(const u32x4* __restrict__ lds,
 // Entry i (0..7) of a thread is LDS row (tid/8) + 32*i, chunk tid%8; entries
 // 0..3 are rows of T-tile ti, entries 4..7 rows of T-tile tj. Stage s < nX
 // reads features [s*KS, ...) of X up to column x1; later stages read features
-// [y0 + (s-nX)*KS, ...) of Y up to column y1. The buffer resources span one
-// example's T rows, so rows past T read as zero; per-row offsets are
-// wave-uniform (SGPR) and only the lane's own (row, chunk) offset is a VGPR.
+// [y0 + (s-nX)*KS, ...) of Y up to column y1.
+// VEC (16-byte rows): buffer loads whose resources span one example's T rows,
+// so rows past T read as zero; per-row offsets are wave-uniform (SGPR) and
+// only the lane's own (row, chunk) offset is a VGPR.
+// Otherwise: 16-byte global loads of any alignment. Rows past T repeat row
+// T-1 and are zeroed on their way to LDS; the stage that holds the last column
+// reads its last chunk element by element. (The norms of GPT-2 at B = 24, T = 100
+// with a V = 50257 head took 516 us with one load per element; 232 us with this.)
 template <int DT, bool VEC>
 struct TileStream {
   static constexpr int EPC = (DT == DT_BF16) ? 8 : 4;
   static constexpr int KS = 8 * EPC;
   static constexpr int ES = (DT == DT_BF16) ? 2 : 4;
   rsrc_t rx, ry;
+  const char *px, *py;         // first row of the example
   uint32_t ldx, ldy;           // row strides in bytes
   uint32_t vxi, vxj, vyi, vyj; // lane offsets of entry 0 / entry 4 in X and Y
+  int ri, rj;                  // this thread's row of entry 0 / entry 4
+  int T;
   int c;                       // this thread's chunk within a row
   int nX;
   int64_t x1, y0, y1;
@@ -229,15 +237,44 @@ struct TileStream {
   template <int NENT>
   __device__ __forceinline__ void prefetch(int s, u32x4 (&pre)[NENT]) const {
     const bool inX = s < nX;
-    const rsrc_t r = inX ? rx : ry;
     const uint32_t ld = inX ? ldx : ldy;
     const int64_t c0 = inX ? (int64_t)s * KS : y0 + (int64_t)(s - nX) * KS;  // stage column
     const int64_t ncol = inX ? x1 : y1;
-    const uint32_t vi = inX ? vxi : vyi, vj = inX ? vxj : vyj;
+    if constexpr (VEC) {
+      const rsrc_t r = inX ? rx : ry;
+      const uint32_t vi = inX ? vxi : vyi, vj = inX ? vxj : vyj;
+#pragma unroll
+      for (int i = 0; i < NENT; ++i) {
+        const uint32_t soff = (uint32_t)(c0 * ES) + (uint32_t)(32 * (i & 3)) * ld;
+        pre[i] = buf_chunk<DT, VEC, true>(r, i < 4 ? vi : vj, soff, c0 + c * EPC, ncol);
+      }
+    } else {
+      const char* p = (inX ? px : py) + c0 * ES;
+      uint32_t off[NENT];
+#pragma unroll
+      for (int i = 0; i < NENT; ++i)
+        off[i] = (uint32_t)min((i < 4 ? ri : rj) + 32 * (i & 3), T - 1) * ld + (uint32_t)c * 16;
+      if (c0 + KS <= ncol) {
+#pragma unroll
+        for (int i = 0; i < NENT; ++i) pre[i] = load16_any(p + off[i]);
+      } else {
+        const int nv = (int)(ncol - (c0 + c * EPC));  // valid elements of this thread's chunk
+#pragma unroll
+        for (int i = 0; i < NENT; ++i)
+          pre[i] = nv >= EPC ? load16_any(p + off[i]) : load16_part<DT>(p + off[i], nv);
+      }
+    }
+  }
+
+  // Writes a stage's entries to LDS.
+  template <int NENT>
+  __device__ __forceinline__ void store(u32x4* lds, const u32x4 (&pre)[NENT], int tid) const {
 #pragma unroll
     for (int i = 0; i < NENT; ++i) {
-      const uint32_t soff = (uint32_t)(c0 * ES) + (uint32_t)(32 * (i & 3)) * ld;
-      pre[i] = buf_chunk<DT, VEC, true>(r, i < 4 ? vi : vj, soff, c0 + c * EPC, ncol);
+      const int r = (tid >> 3) + 32 * i, cc = tid & 7;
+      u32x4 v = pre[i];
+      if (!VEC && (i < 4 ? ri : rj) + 32 * (i & 3) >= T) v = u32x4{0u, 0u, 0u, 0u};
+      lds[r * 8 + swz(r, cc)] = v;
     }
   }
 };
@@ -270,6 +307,9 @@ __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int
   ts.ldy = (uint32_t)(L.ldg * TS::ES);
   ts.rx = make_rsrc((const char*)L.A + ex_rows * ts.ldx, (uint64_t)T * ts.ldx);
   ts.ry = make_rsrc((const char*)L.G + ex_rows * ts.ldy, (uint64_t)T * ts.ldy);
+  ts.px = (const char*)L.A + ex_rows * ts.ldx;
+  ts.py = (const char*)L.G + ex_rows * ts.ldy;
+  ts.T = T;
   ts.c = tid & 7;
   ts.x1 = L.d_in;
   ts.y0 = (int64_t)L.g0 + (int64_t)chunk * L.kg;
@@ -277,6 +317,8 @@ __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int
   ts.nX = ((L.d_in + TS::KS - 1) / TS::KS + 1) & ~1;  // padded to even
   const int nY = (int)((ts.y1 - ts.y0 + TS::KS - 1) / TS::KS);
   const uint32_t r0 = tid >> 3, cb = (tid & 7) * 16;
+  ts.ri = ti * GR_TM + (int)r0;
+  ts.rj = tj * GR_TM + (int)r0;
   ts.vxi = (ti * GR_TM + r0) * ts.ldx + cb;
   ts.vxj = (tj * GR_TM + r0) * ts.ldx + cb;
   ts.vyi = (ti * GR_TM + r0) * ts.ldy + cb;
@@ -305,18 +347,18 @@ __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int
       for (int s = s_begin; s < s_end; s += 2) {
         if (s + 2 < n) ts.template prefetch<NENT>(s + 2, pA);
         stage_mfma<DT, NB>(buf0, ra, rb, acc, lane);
-        if (s + 1 < n) store_stage<NENT>(buf1, pB, tid);
+        if (s + 1 < n) ts.template store<NENT>(buf1, pB, tid);
         __syncthreads();
         if (s + 1 >= s_end) break;
         if (s + 3 < n) ts.template prefetch<NENT>(s + 3, pB);
         stage_mfma<DT, NB>(buf1, ra, rb, acc, lane);
-        if (s + 2 < n) store_stage<NENT>(buf0, pA, tid);
+        if (s + 2 < n) ts.template store<NENT>(buf0, pA, tid);
         __syncthreads();
       }
     };
     ts.template prefetch<NENT>(0, pA);
     if (n > 1) ts.template prefetch<NENT>(1, pB);
-    store_stage<NENT>(buf0, pA, tid);
+    ts.template store<NENT>(buf0, pA, tid);
     __syncthreads();
     phase(0, ts.nX, accP);
     phase(ts.nX, n, accQ);
@@ -328,12 +370,12 @@ __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int
       for (int s = s_begin; s < s_end; ++s) {
         if (s + 1 < n) ts.template prefetch<NENT>(s + 1, pA);
         stage_mfma<DT, NB>((s & 1) ? buf1 : buf0, ra, rb, acc, lane);
-        if (s + 1 < n) store_stage<NENT>((s & 1) ? buf0 : buf1, pA, tid);
+        if (s + 1 < n) ts.template store<NENT>((s & 1) ? buf0 : buf1, pA, tid);
         __syncthreads();
       }
     };
     ts.template prefetch<NENT>(0, pA);
-    store_stage<NENT>(buf0, pA, tid);
+    ts.template store<NENT>(buf0, pA, tid);
     __syncthreads();
     phase(0, ts.nX, accP);
     phase(ts.nX, n, accQ);
