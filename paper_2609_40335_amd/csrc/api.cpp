@@ -195,23 +195,24 @@ int pick_chunks(int64_t width, int ks, int64_t items_per_chunk, int64_t other, i
   return (int)best;
 }
 
-// Widest G chunk, in stages, of a Gram launch whose unchunked items would not
-// occupy every compute unit once: an item's stages are a serial chain (about
-// 0.5 us each), so such a launch takes as long as its longest item. Narrower
-// chunks shorten it and fill idle compute units, and each one repeats the
-// layer's A stages. The choice minimises max(longest item, stages per
-// workgroup slot), with GRAM_FILL stages per item for filling the ring and
-// reducing the partials. (d_in = 768, d_out = 3072, B = 24, T = 128:
-// the norm took 34 us of 109 for norm and sum, 12 of 87 with it.) A launch of a full round or more keeps its items:
-// each chunk's repeated A stages then cost more than the shorter tail gains.
+// Widest G chunk, in stages, for the layers that pick_chunks leaves whole, in
+// a Gram launch whose items would not occupy every workgroup slot once: an
+// item's stages are a serial chain (about 0.5 us each), so such a launch takes
+// as long as its longest item. Narrower chunks shorten it and fill idle
+// compute units, and each one repeats the layer's A stages. The choice
+// minimises max(longest item, stages per workgroup slot), with GRAM_FILL
+// stages per item for filling the ring and reducing the partials. (d_in = 768,
+// d_out = 3072, B = 24, T = 128: the norm took 34 us of 109 for norm and sum,
+// 12 of 87 with it.) A launch of a full round or more keeps its items: each
+// chunk's repeated A stages then cost more than the shorter tail gains.
 constexpr int GRAM_FILL = 6;
 struct GramShape {
   int64_t items, nx, ny;  // items per chunk; stages of A, of G
 };
-int few_items_chunk(const std::vector<GramShape>& v, int64_t slots) {
-  int64_t items = 0;
+int few_items_chunk(const std::vector<GramShape>& v, int64_t other, int64_t slots) {
+  int64_t items = other;
   for (const GramShape& g : v) items += g.items;
-  if (items >= slots) return 0;
+  if (v.empty() || items >= slots) return 0;
   int best = 0;
   double best_cost = 0;
   for (int q : {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
@@ -221,7 +222,7 @@ int few_items_chunk(const std::vector<GramShape>& v, int64_t slots) {
       longest = std::max(longest, len);
       total += g.items * ceil_div(g.ny, q) * len;
     }
-    const double cost = std::max((double)longest, (double)total / (double)slots);
+    const double cost = std::max((double)longest, (double)total / (double)(slots - other));
     if (best == 0 || cost <= best_cost) { best = q; best_cost = cost; }
   }
   return best;
@@ -233,8 +234,12 @@ NormPlan plan_norm(const dp_linear_t* layers, int n, int B, int T, dp_dtype_t dt
   p.n_t = (int)ceil_div(T, dpg::GR_TM);
   p.P = p.n_t * (p.n_t + 1) / 2;
   const int ks = stage_features(dt);
-  // <P, Q> is symmetric in A and G; the chunked side (the second) of a launch
-  // of few items is the wider one, unless the layer's bias rides on G.
+  const int64_t slots = (int64_t)device_cus() * dpg::gram_groups_per_cu(T);
+  auto vec_of = [&](const dp_linear_t& L) {
+    return vec_ok(L.A, L.lda, dt) && vec_ok(L.G, L.ldg, dt);
+  };
+  // <P, Q> is symmetric in A and G; the chunked side (the second) of a layer
+  // of a launch of few items is the wider one, unless its bias rides on G.
   auto swapped = [&](int i) {
     return !(bias && bias[i]) && layers[i].d_in > layers[i].d_out;
   };
@@ -243,18 +248,27 @@ NormPlan plan_norm(const dp_linear_t* layers, int n, int B, int T, dp_dtype_t dt
   std::vector<GramShape> shapes[2];
   for (int i = 0; i < n; ++i) {
     const dp_linear_t& L = layers[i];
-    if (use_direct(L, T)) continue;
-    const bool vec = vec_ok(L.A, L.lda, dt) && vec_ok(L.G, L.ldg, dt);
+    if (use_direct(L, T) || L.d_out > KG_SPLIT) continue;
+    const bool vec = vec_of(L);
     const int64_t items = (int64_t)B * gram_pairs(p, dt, vec, T);
     const bool sw = swapped(i);
     shapes[vec].push_back({items, ceil_div(sw ? L.d_out : L.d_in, ks),
                            ceil_div(sw ? L.d_in : L.d_out, ks)});
-    if (L.d_out <= KG_SPLIT) plain_items[vec] += items;
+    plain_items[vec] += items;
+  }
+  std::vector<int> width(n, 0);       // features per chunk of the layers longer than KG_SPLIT
+  int64_t wide_items[2] = {0, 0};
+  for (int i = 0; i < n; ++i) {
+    const dp_linear_t& L = layers[i];
+    if (use_direct(L, T) || L.d_out <= KG_SPLIT) continue;
+    const bool vec = vec_of(L);
+    const int64_t per_chunk = (int64_t)B * gram_pairs(p, dt, vec, T);
+    const int nc = pick_chunks(L.d_out, ks, per_chunk, plain_items[vec] + wide_items[vec], slots);
+    width[i] = (int)(ceil_div(ceil_div(L.d_out, nc), ks) * ks);
+    wide_items[vec] += per_chunk * ceil_div(L.d_out, width[i]);
   }
   int few[2];  // stages per G chunk where a launch is short of items, else 0
-  for (int v = 0; v < 2; ++v)
-    few[v] = shapes[v].empty() ? 0 : few_items_chunk(
-        shapes[v], (int64_t)device_cus() * dpg::gram_groups_per_cu(T));
+  for (int v = 0; v < 2; ++v) few[v] = few_items_chunk(shapes[v], wide_items[v], slots);
   for (int i = 0; i < n; ++i) {
     const dp_linear_t& L = layers[i];
     float* const bg = bias ? bias[i] : nullptr;
@@ -263,20 +277,12 @@ NormPlan plan_norm(const dp_linear_t* layers, int n, int B, int T, dp_dtype_t dt
       if (bg) p.bias_vec.push_back({L.G, L.ldg, L.d_out, bg});
       continue;
     }
-    const bool vec = vec_ok(L.A, L.lda, dt) && vec_ok(L.G, L.ldg, dt);
-    int kg = (int)(ceil_div(L.d_out, ks) * ks);
-    if (few[vec]) {
-      kg = few[vec] * ks;
-    } else if (L.d_out > KG_SPLIT) {
-      const int64_t per_chunk = (int64_t)B * gram_pairs(p, dt, vec, T);
-      const int64_t slots = (int64_t)device_cus() * dpg::gram_groups_per_cu(T);
-      const int nc = pick_chunks(L.d_out, ks, per_chunk, plain_items[vec], slots);
-      kg = (int)(ceil_div(ceil_div(L.d_out, nc), ks) * ks);
-      plain_items[vec] += per_chunk * ceil_div(L.d_out, kg);
-    }
+    const bool vec = vec_of(L);
+    const bool chunk = few[vec] && L.d_out <= KG_SPLIT;
+    const int kg = width[i] ? width[i] : chunk ? few[vec] * ks : (int)(ceil_div(L.d_out, ks) * ks);
     GramEntry e{L.A, L.G, L.lda, L.ldg, L.d_in, 0, L.d_out, kg, (int)ceil_div(L.d_out, kg),
                 (int)p.slots, vec};
-    if (few[vec] && swapped(i))
+    if (chunk && swapped(i))
       e = GramEntry{L.G, L.A, L.ldg, L.lda, L.d_out, 0, L.d_in, kg, (int)ceil_div(L.d_in, kg),
                     (int)p.slots, vec};
     if (bg) {
@@ -414,10 +420,10 @@ dp_status_t run_gemm(const std::vector<GemmEntry>& entries, int mode, int B, int
     a.sigma_c = nz.sigma_c; a.inv_b = nz.inv_b; a.step = nz.step; a.seed = nz.seed;
     a.part = part;
     a.eg = 1;
-    if (mode == 1 && kdt(dt) == dpg::DT_BF16 && vec && T % dpg::DL_SUM_BK == 0) {
+    if (mode == 1 && kdt(dt) == dpg::DT_BF16) {
       uint64_t tiles = 0;
       for (const GemmEntry* e : sel) tiles += (uint64_t)e->tm * e->tn;
-      a.eg = dpg::norm_group(tiles, B, T / dpg::DL_SUM_BK, device_cus());
+      a.eg = dpg::norm_group(tiles, B, (int)ceil_div(T, dpg::DL_SUM_BK), device_cus());
     }
     const uint64_t groups = (uint64_t)((B + a.eg - 1) / a.eg);
     uint64_t items = 0;

@@ -170,11 +170,14 @@ __device__ __forceinline__ u32x4 buf_chunk(rsrc_t r, uint32_t voff, uint32_t sof
   return v;
 }
 
-// 16 bytes from an address of any alignment (one global_load_dwordx4).
+// 16 bytes of global memory at an address of any alignment: one
+// global_load_dwordx4. (The address space is spelt out: a generic load counts
+// as an LDS access too, and every wait for LDS would wait for it.)
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef const __attribute__((address_space(1))) u32x4_any global_u32x4_any;
+typedef const __attribute__((address_space(1))) uint16_t global_u16;
 __device__ __forceinline__ u32x4 load16_any(const char* p) {
-  u32x4 v;
-  __builtin_memcpy(&v, p, 16);
-  return v;
+  return *(global_u32x4_any*)(uintptr_t)p;
 }
 
 // Elements [0, n) of the 16-byte chunk at p, n below a chunk's count; the

@@ -190,6 +190,21 @@ __device__ __forceinline__ float noise_at(const GemmArgs& a, uint32_t tid, uint6
   return q == 0 ? z[0] : q == 1 ? z[1] : q == 2 ? z[2] : z[3];
 }
 
+// The draws of 4 consecutive elements j0 .. j0+3 of a tensor: one Philox block
+// where j0 is a multiple of 4, parts of two otherwise.
+__device__ __forceinline__ void noise4_at(const GemmArgs& a, uint32_t tid, uint64_t j0,
+                                          float (&z)[4]) {
+  gauss4(j0 >> 2, a.seed, tid, a.step, z);
+  const int sh = (int)(j0 & 3);
+  if (sh != 0) {
+    float y[4];
+    gauss4((j0 >> 2) + 1, a.seed, tid, a.step, y);
+    const float x[7] = {z[0], z[1], z[2], z[3], y[0], y[1], y[2]};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) z[k] = sh == 1 ? x[k + 1] : sh == 2 ? x[k + 2] : x[k + 3];
+  }
+}
+
 __device__ __forceinline__ void store_tile(const GemmArgs& a, const GemmLayer& L, int64_t m0,
                                            int64_t n0, int wm, int wn, int lane,
                                            f32x16 (&acc)[4][2], bool transposed) {
@@ -278,17 +293,18 @@ __device__ __forceinline__ void store_tile_rows(const GemmArgs& a, const GemmLay
   const bool accum = L.accumulate != 0;
   const bool noise = a.noise != 0;
   const uint32_t tid = L.tensor_id;
-  const bool full = m0 + GM_BM <= L.M && n0 + GM_BN <= L.N;
-  const bool vec = full && (ldo & 3) == 0 && (((uintptr_t)out) & 15) == 0 && (L.N & 3) == 0;
+  // Rows of whole aligned float4s: a float4 lies in the matrix or outside it.
+  const bool vec = (ldo & 3) == 0 && (((uintptr_t)out) & 15) == 0 && (L.N & 3) == 0;
   const int rw = (lane >> 5) * 4;  // row of e = 0 within a block
   const int cw = lane & 31;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
+      const int64_t mb = m0 + wm * 128 + i * 32, nb = n0 + wn * 64 + j * 32;
+      if (mb >= L.M || nb >= L.N) continue;  // a block wholly past the matrix
 #pragma unroll
       for (int e = 0; e < 16; ++e) slice[(rw + (e >> 2) * 8 + (e & 3)) * EP_LD + cw] = acc[i][j][e];
-      const int64_t mb = m0 + wm * 128 + i * 32, nb = n0 + wn * 64 + j * 32;
       // The block's 4 float4s per lane: prior values (when accumulating) are
       // requested first and the noise is drawn while they are in flight.
       const int c4 = 4 * (lane & 7);
@@ -300,10 +316,13 @@ __device__ __forceinline__ void store_tile_rows(const GemmArgs& a, const GemmLay
         v[it] = *(const f32x4*)(slice + r * EP_LD + c4);
       }
       if (vec) {
+        const bool nin = n < L.N;
         if (accum) {
 #pragma unroll
-          for (int it = 0; it < 4; ++it)
-            prior[it] = *(const f32x4*)(out + (mb + (lane >> 3) + 8 * it) * ldo + n);
+          for (int it = 0; it < 4; ++it) {
+            const int64_t m = mb + (lane >> 3) + 8 * it;
+            if (nin && m < L.M) prior[it] = *(const f32x4*)(out + m * ldo + n);
+          }
         }
         if (noise) {
 #pragma unroll
@@ -321,7 +340,7 @@ __device__ __forceinline__ void store_tile_rows(const GemmArgs& a, const GemmLay
           f32x4 x = v[it];
           if (accum) x += prior[it];
           if (noise) x *= a.inv_b;
-          __builtin_nontemporal_store(x, (f32x4*)(out + m * ldo + n));
+          if (nin && m < L.M) __builtin_nontemporal_store(x, (f32x4*)(out + m * ldo + n));
         }
       } else {
 #pragma unroll
@@ -329,13 +348,13 @@ __device__ __forceinline__ void store_tile_rows(const GemmArgs& a, const GemmLay
           const int64_t m = mb + (lane >> 3) + 8 * it;
           if (m >= L.M) continue;
           float* p = out + m * ldo + n;
+          float z[4];
+          if (noise) noise4_at(a, tid, (uint64_t)m * (uint64_t)L.N + n, z);
 #pragma unroll
           for (int q = 0; q < 4; ++q)
             if (n + q < L.N) {
               float x = (accum ? p[q] : 0.f) + v[it][q];
-              if (noise)
-                x = (x + a.sigma_c * noise_at(a, tid, (uint64_t)m * (uint64_t)L.N + n + q)) *
-                    a.inv_b;
+              if (noise) x = (x + a.sigma_c * z[q]) * a.inv_b;
               p[q] = x;
             }
         }
@@ -403,13 +422,13 @@ __global__ __launch_bounds__(256) void split_fixup_kernel(GemmArgs args) {
     if (noise) v *= a.inv_b;
     *(f32x4*)p = v;
   } else {
+    float z[4];
+    if (noise) noise4_at(a, L.tensor_id, (uint64_t)m * (uint64_t)L.N + n, z);
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (n + k < L.N) {
         float x = (accum ? p[k] : 0.f) + v[k];
-        if (noise)
-          x = (x + a.sigma_c * noise_at(a, L.tensor_id, (uint64_t)m * (uint64_t)L.N + n + k)) *
-              a.inv_b;
+        if (noise) x = (x + a.sigma_c * z[k]) * a.inv_b;
         p[k] = x;
       }
   }
@@ -589,7 +608,8 @@ __global__ __launch_bounds__(GM_THREADS) void kt_gemm_kernel(GemmArgs args) {
   }
 
   if constexpr (MODE == MODE_SUM) {
-    store_tile(a, L, m0, n0, wm, wn, lane, acc, a.transpose != 0);
+    // The host orders every launch so that the kernel's rows are the output's.
+    store_tile_rows(a, L, m0, n0, wm, wn, lane, acc, (float*)&Xs[0][0] + w * 32 * EP_LD);
   } else {
     float part = 0.f;
 #pragma unroll
@@ -710,9 +730,13 @@ __device__ __forceinline__ size_t store_chunk(int i, int j, int q) {
   return (size_t)((i * 2 + j) * 4 + q) * 256;
 }
 
-// BIG: some operand of the launch spans 4 GiB or more (see issue()).
-template <int MODE, bool BIG>
+// FORM: how the launch's stages are cut and loaded (see GemmForm).
+template <int MODE, int FORM>
 __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
+  constexpr bool BIG = FORM == FORM_BIG;
+  constexpr bool STAGED = FORM == FORM_STAGED || FORM == FORM_ROWS;  // through registers
+  constexpr bool WHOLE = FORM == FORM_PLAIN || FORM == FORM_BIG;     // T a multiple of DL_BK
+  constexpr bool ROWS = FORM == FORM_ROWS;
   const GemmArgs& a = *(const GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   (void)args;
   __shared__ __attribute__((aligned(1024))) char ring_raw[DL_NS * DL_STB];
@@ -735,12 +759,16 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
   const GemmLayer& L = a.L[l];
   uint32_t rel = item - L.tile_begin;
   const int64_t K = (int64_t)a.B * a.T;
+  // Stages: DL_BK rows each, cut per example (the last one of an example may
+  // be short) or, with ROWS, over all K rows. This item covers stages gs0 ..
+  // gs0 + nS - 1 of the launch.
+  const int spe = (a.T + DL_BK - 1) / DL_BK;  // stages per example
   int b = 0;
-  int64_t k_begin = 0, k_end = K;
+  int gs0 = 0, nS = ROWS ? (int)((K + DL_BK - 1) / DL_BK) : a.B * spe;
   if (MODE == MODE_SUM && kc >= 0) {
-    const int64_t per = (K / DL_BK + a.ksplit - 1) / a.ksplit * DL_BK;  // rows per range
-    k_begin = kc * per;
-    k_end = k_begin + per < K ? k_begin + per : K;
+    const int per = (nS + a.ksplit - 1) / a.ksplit;  // stages per range
+    gs0 = kc * per;
+    nS = gs0 + per < nS ? per : (gs0 < nS ? nS - gs0 : 0);
   }
   int n_ex = 1;  // direct norm: examples b .. b + n_ex - 1 of this item
   if constexpr (MODE == MODE_NORM) {
@@ -749,9 +777,13 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
     rel -= (uint32_t)grp * ntile;
     b = grp * a.eg;
     n_ex = a.B - b < a.eg ? a.B - b : a.eg;
-    k_begin = (int64_t)b * a.T;
-    k_end = k_begin + (int64_t)n_ex * a.T;
+    gs0 = b * spe;
+    nS = n_ex * spe;
   }
+  // First row of the item, and the end of the example it lies in.
+  const int e0 = ROWS ? 0 : gs0 / spe;
+  const int64_t k_begin = ROWS ? (int64_t)gs0 * DL_BK
+                               : (int64_t)e0 * a.T + (int64_t)(gs0 - e0 * spe) * DL_BK;
   int mt, nt;
   tile_of(L, rel, mt, nt);
   const int64_t m0 = (int64_t)mt * GM_BM;
@@ -782,14 +814,50 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(gbase >> 32)),
                       (uint32_t)__builtin_amdgcn_readfirstlane((int)nrec), (uint32_t)RSRC_WORD3};
   const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
-  const int nS = (int)((k_end - k_begin) / DL_BK);
   // Load t (of DL_LOADS) of this wave's share of stage s.
   // An operand of 4 GiB or more does not fit the 32-bit offsets: its
   // descriptor's base moves to each stage's first row instead (the records
   // left from there, none past the last stage). A separate instance, so that
   // launches without such an operand keep the plain loop.
   const bool big = BIG && nrec64 > 0xFFFFFFFFull;
+  // Examples of any length: the stages to load are visited in order, so the
+  // first row of the next one and the end of its example are carried along. The descriptor starts at that
+  // row and ends with the example: rows past it read as zeros, and no offset
+  // grows with the operand.
+  struct Cursor {
+    uint64_t base;   // address of this wave's first row of the stage
+    int left;        // rows left from the stage's first row to the example's end
+  };
+  auto uniform64 = [](uint64_t x) {  // keeps wave-uniform arithmetic on the scalar unit
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+  };
+  const int nT = __builtin_amdgcn_readfirstlane(a.T);
+  const uint32_t ld_u = (uint32_t)__builtin_amdgcn_readfirstlane((int)ld_bytes);
+  Cursor ld_at{uniform64(gbase + (uint64_t)(k_begin + wq * 8) * ld_bytes),
+               __builtin_amdgcn_readfirstlane(ROWS ? (int)min(K - k_begin, (int64_t)INT32_MAX)
+                                                   : (int)((int64_t)(e0 + 1) * a.T - k_begin))};
+  auto next_stage = [&](Cursor& q) {
+    const int step = q.left < DL_BK ? q.left : DL_BK;
+    q.base += (uint64_t)ld_u * (uint32_t)step;
+    q.left -= step;
+    if (!ROWS && q.left == 0) q.left = nT;
+  };
   auto issue = [&](int s, int t) {
+    if constexpr (!WHOLE) {
+      const uint32_t dst = ring_base + (uint32_t)((s % DL_NS) * DL_STB) + lds_role;
+      const int rows = ld_at.left - wq * 8;  // from this wave's first row on
+      const uint32_t nr = s < nS && rows > 0 ? (uint32_t)rows * ld_u : 0u;
+      const u32x4 d = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)ld_at.base),
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ld_at.base >> 32)),
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)nr), (uint32_t)RSRC_WORD3};
+      const uint32_t m0v = (uint32_t)__builtin_amdgcn_readfirstlane((int)(dst + t * 1024));
+      const uint32_t so = (uint32_t)__builtin_amdgcn_readfirstlane((int)(2 * t * ld_u));
+      asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen sc1 lds"
+                   :: "s"(m0v), "v"(lvo[t & 1]), "s"(d), "s"(so));
+      if (t == DL_LOADS - 1) next_stage(ld_at);
+      return;
+    }
     const uint32_t dst = ring_base + (uint32_t)((s % DL_NS) * DL_STB) + lds_role;
     const int64_t row0 = k_begin + (int64_t)s * DL_BK + wq * 8;
     uint32_t sbase;
@@ -845,17 +913,23 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
   if constexpr (MODE == MODE_SUM)
-    for (int i = tid; i < a.B; i += GM_THREADS) cs[i] = a.c[i];
-  const int spe = a.T / DL_BK;  // stages per example
+    for (int i = tid; i < min(a.B, DL_MAXB); i += GM_THREADS) cs[i] = a.c[i];
+  // A batch of more examples than the table holds reads the factors of the
+  // others from memory.
+  auto factor = [&](int e) {
+    if (WHOLE || e < DL_MAXB) return cs[e];
+    float x = a.c[e];
+    // Opaque: merged with the other load it would be one load through a
+    // generic pointer, whose wait drains the ring.
+    asm volatile("" : "+v"(x));
+    return x;
+  };
   // Held in a register: a kernel-argument read inside the loop would be a
   // scalar load whose wait (lgkmcnt) also waits for every LDS read in flight.
   const int nB = __builtin_amdgcn_readfirstlane(a.B);
-  // Stage indices below are local to this item's K range, which starts at
-  // global stage gs0, inside example e0 (at its start unless this is a split
-  // range): the first stage is treated as a boundary, where nothing is yet
-  // accumulated.
-  const int gs0 = (int)(k_begin / DL_BK);
-  const int e0 = gs0 / spe;
+  // Stage indices below are local to this item, whose stages may start inside
+  // example e0 (a split range): the first stage is treated as a boundary,
+  // where nothing is yet accumulated.
   float c_acc = 0.f;            // factor of what is accumulated; 0: nothing yet
   float c_nx = 0.f;             // factor of the example that starts at stage s_nx
   bool skip = false;
@@ -925,16 +999,16 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
   // accumulators by c_prev / c_next and fetches the factor of the example
   // after. Direct norm: at an example boundary, reduces the finished
   // example's part of the tile and clears the accumulators.
-  auto enter = [&](int s) {
+  auto enter = [&](int s) __attribute__((always_inline)) {
     if (MODE == MODE_NORM && s == s_nx) {
       fin();
       s_nx += spe;
     }
-    if (MODE == MODE_SUM && s == s_nx) {
+    if (MODE == MODE_SUM && !ROWS && s == s_nx) {
       const float ce = c_nx;
       ++e_nx;
       s_nx = e_nx * spe - gs0;
-      if (e_nx < nB) c_nx = cs[e_nx];
+      if (e_nx < nB) c_nx = factor(e_nx);
       skip = !(ce != 0.f);
       if (!skip) {
         if (c_acc != 0.f) {
@@ -996,14 +1070,159 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
   };
 
   u32x4 fr[12];
-  if (w < 4) {
+  if constexpr (STAGED) {
+    // Register-staged loads (rows of any alignment, waves 0-3 X, waves 4-7
+    // Y as above): in the memory phase of stage s both groups write stage s + 2
+    // to LDS (the slot of stage s - 2) and load stage s + 3 into the same
+    // registers, one stage's time before their write. (Two sets, loaded two
+    // stages ahead, do not fit the register file.) Lane l takes rows 2t + l/32, logical chunk l%32, so a
+    // row's 512 bytes are read in order.
+    const int64_t ncol = load_x ? L.M : L.N;
+    const int ncl = (int)min(ncol - (col0 + 8 * (lane & 31)), (int64_t)8);  // of this lane's 8
+    const uint32_t lo0 = (uint32_t)((lane >> 5) * ld_bytes + (lane & 31) * 16);
+    typedef u32x4 Set[DL_LOADS];
+    // Address of the tile's first column in this wave's first row of a stage.
+    // Chunks past the matrix's columns read the row's padding or the next
+    // row, and only feed outputs that are not stored; what must not happen is
+    // a read past the matrix's end. `tight`: some chunk of these 8 rows would.
+    // (As a signed offset from the end back: the tile's reach past its first
+    // row's start, and one lane chunk's.)
+    const uint64_t mend = uniform64(gbase + (uint64_t)K * ld_bytes);
+    const uint64_t col_b = uniform64((uint64_t)col0 * 2);
+    const uint64_t reach = 7ull * ld_u + col_b + GM_BM * 2;
+    auto at = [&](const Cursor& q) { return (const char*)(q.base + col_b); };
+    auto tight = [&](const Cursor& q) { return q.base + reach > mend; };
+    // `lo`: the lane's offset, copied where it is used so that no address
+    // derived from it is kept in registers across the loop.
+    auto fresh = [](uint32_t x) {
+      asm volatile("" : "+v"(x));
+      return x;
+    };
+    auto in_span = [&](const Cursor& q, int t, uint32_t lo) {  // the lane's chunk of row 2t + lane / 32
+      return q.base + col_b + (uint64_t)(2 * t) * ld_u + lo + 16 <= mend;
+    };
+    auto load_set = [&](int s, Set& q) __attribute__((always_inline)) {
+      if (s >= nS) return;
+      const char* p = at(ld_at);
+      const int rows = ld_at.left - wq * 8;  // rows left from this wave's first
+      const uint32_t lo = fresh(lo0);
+      if (!tight(ld_at)) {
+        // Rows past the example repeat its last row here (or, where the wave
+        // has none of its rows, are not read) and are zeroed when written.
+        if (rows >= 8) {
+#pragma unroll
+          for (int t = 0; t < DL_LOADS; ++t) q[t] = load16_any(p + (size_t)(2 * t) * ld_u + lo);
+        } else if (rows > 0) {
+          const uint32_t odd = lane < 32 ? lo : lo - ld_u;  // the lane's offset in an even row
+#pragma unroll
+          for (int t = 0; t < DL_LOADS; ++t)
+            q[t] = load16_any(p + (size_t)min(2 * t, rows - 1) * ld_u +
+                              (2 * t + 1 < rows ? lo : odd));
+        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < DL_LOADS; ++t) {
+          q[t] = u32x4{0u, 0u, 0u, 0u};
+          if (2 * t + (lane >> 5) < rows && in_span(ld_at, t, lo))
+            q[t] = load16_any(p + (size_t)(2 * t) * ld_u + lo);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      next_stage(ld_at);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    Cursor wr_at = ld_at;
+    // ROWS: example and row within it of this wave's first row of the next
+    // stage to write; row r0w + j lies (r0w + j) / T examples on, and
+    // x / T = hi32(x * rcpT) for the x < T + DL_BK here (T <= 2 DL_BK).
+    int e_wr = ROWS ? (int)((k_begin + wq * 8) / a.T) : 0;
+    int r_wr = ROWS ? (int)((k_begin + wq * 8) - (int64_t)e_wr * a.T) : 0;
+    const uint32_t rcpT = 0xFFFFFFFFu / (uint32_t)nT + 1u;
+    auto write_set = [&](int s, Set& q) __attribute__((always_inline)) {
+      if (s >= nS) return;
+      char* dst = ring_raw + (s % DL_NS) * DL_STB + lds_role;
+      const int rows = wr_at.left - wq * 8;
+      const bool edge = tight(wr_at);
+#pragma unroll
+      for (int t = 0; t < DL_LOADS; ++t) {
+        const uint32_t lo = fresh(lo0);
+        const int lf = (int)fresh((uint32_t)lane);
+        const int r = 2 * t + (lf >> 5);
+        float c = 1.f;
+        if constexpr (ROWS) {
+          const int x = r_wr + r;
+          c = factor(min(e_wr + (nT == 1 ? x : (int)__umulhi((uint32_t)x, rcpT)), nB - 1));
+          // X rows scaled by their example's factor; the rows of an example
+          // with c = 0 are zeroed in both operands (0 * inf would be NaN).
+          if (load_x) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[t][k] = scale_bf16x2(q[t][k], c);
+          }
+          if (c == 0.f) q[t] = u32x4{0u, 0u, 0u, 0u};
+        }
+        if (rows < 8 && r >= rows) q[t] = u32x4{0u, 0u, 0u, 0u};
+        char* const d = dst + r * DL_ROWB + (((lf & 31) ^ dl_sw(r)) << 4);
+        *(u32x4*)d = q[t];
+        // The chunk that would read past the matrix's end, element by element.
+        if (edge && r < rows && c != 0.f && ncl > 0 && !in_span(wr_at, t, lo)) {
+          global_u16* src = (global_u16*)(uintptr_t)(at(wr_at) + (size_t)(2 * t) * ld_u + lo);
+#pragma unroll 1
+          for (int k = 0; k < ncl; ++k) {
+            uint32_t v = src[k];
+            if (ROWS && load_x) v = scale_bf16x2(v, c);
+            ((uint16_t*)d)[k] = (uint16_t)v;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (ROWS) {
+        const int x = r_wr + DL_BK;
+        const int de = nT == 1 ? x : (int)__umulhi((uint32_t)x, rcpT);
+        e_wr += de;
+        r_wr = x - de * nT;
+      }
+      next_stage(wr_at);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    Set q;
+    load_set(0, q);
+    write_set(0, q);
+    load_set(1, q);
+    write_set(1, q);
+    load_set(2, q);
+    bar();
+    if constexpr (MODE == MODE_SUM && !ROWS) c_nx = factor(min(e0, nB - 1));
+    if (w < 4) {
+      rd(0, fr);
+      enter(0);
+      for (int s = 0; s < nS; ++s) {
+        compute(fr);
+        bar();
+        write_set(s + 2, q);
+        load_set(s + 3, q);
+        rd(s + 1, fr);
+        if (s + 1 < nS) enter(s + 1);
+        bar();
+      }
+    } else {
+      for (int s = 0; s < nS; ++s) {
+        write_set(s + 2, q);
+        load_set(s + 3, q);
+        rd(s, fr);
+        enter(s);
+        bar();
+        compute(fr);
+        bar();
+      }
+    }
+  } else if (w < 4) {
 #pragma unroll
     for (int p = 0; p < DL_NS; ++p)
 #pragma unroll
       for (int t = 0; t < DL_LOADS; ++t) issue(p, t);
     wait_vmcnt<DL_LOADS * (DL_NS - 1)>();
     bar();  // stage 0 has landed, the factor table is filled
-    if constexpr (MODE == MODE_SUM) c_nx = cs[e0];
+    if constexpr (MODE == MODE_SUM) c_nx = factor(min(e0, nB - 1));
     rd(0, fr);
     enter(0);
     for (int s = 0; s < nS; ++s) {
@@ -1021,7 +1240,7 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
       for (int t = 0; t < DL_LOADS; ++t) issue(p, t);
     wait_vmcnt<DL_LOADS * (DL_NS - 2)>();
     bar();
-    if constexpr (MODE == MODE_SUM) c_nx = cs[e0];
+    if constexpr (MODE == MODE_SUM) c_nx = factor(min(e0, nB - 1));
     for (int s = 0; s < nS; ++s) {
       rd_issue(s, s + DL_NS - 1, fr);
       enter(s);
@@ -1034,10 +1253,12 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
   // No load may still be writing LDS when the workgroup ends.
   wait_vmcnt<0>();
   if constexpr (MODE == MODE_SUM) {
+    if constexpr (!ROWS) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] *= c_acc;
+        for (int j = 0; j < 2; ++j) acc[i][j] *= c_acc;
+    }
     if (kc >= 0) {
       // A split range: its raw partial tile, for the fixup kernel.
       __syncthreads();
@@ -1135,16 +1356,33 @@ hipError_t launch_store_sum(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int DT, bool VEC, int MODE>
-static void launch_sc(const GemmArgs& a, int sc, hipStream_t s) {
+template <bool VEC, int MODE>
+static void launch_f32(const GemmArgs& a, hipStream_t s) {
   const dim3 g(a.n_items), blk(GM_THREADS);
   if constexpr (MODE == MODE_NORM) {
-    hipLaunchKernelGGL((kt_gemm_kernel<DT, VEC, MODE, SC_NONE>), g, blk, 0, s, a);
+    hipLaunchKernelGGL((kt_gemm_kernel<DT_F32, VEC, MODE, SC_NONE>), g, blk, 0, s, a);
   } else {
-    if (sc == SC_ACC)
-      hipLaunchKernelGGL((kt_gemm_kernel<DT, VEC, MODE, SC_ACC>), g, blk, 0, s, a);
+    // The accumulator form needs every K-stage inside one example.
+    if (a.T % KT<DT_F32>::KS == 0)
+      hipLaunchKernelGGL((kt_gemm_kernel<DT_F32, VEC, MODE, SC_ACC>), g, blk, 0, s, a);
     else
-      hipLaunchKernelGGL((kt_gemm_kernel<DT, VEC, MODE, SC_STAGE>), g, blk, 0, s, a);
+      hipLaunchKernelGGL((kt_gemm_kernel<DT_F32, VEC, MODE, SC_STAGE>), g, blk, 0, s, a);
+  }
+}
+
+template <int MODE>
+static void launch_dl(const GemmArgs& a, int form, uint32_t grid, hipStream_t s) {
+  const dim3 g(grid), blk(GM_THREADS);
+  if (form == FORM_PLAIN) {
+    hipLaunchKernelGGL((dl_gemm_kernel<MODE, FORM_PLAIN>), g, blk, 0, s, a);
+  } else if (form == FORM_BIG) {
+    hipLaunchKernelGGL((dl_gemm_kernel<MODE, FORM_BIG>), g, blk, 0, s, a);
+  } else if (form == FORM_RAGGED) {
+    hipLaunchKernelGGL((dl_gemm_kernel<MODE, FORM_RAGGED>), g, blk, 0, s, a);
+  } else if (form == FORM_STAGED) {
+    hipLaunchKernelGGL((dl_gemm_kernel<MODE, FORM_STAGED>), g, blk, 0, s, a);
+  } else if constexpr (MODE == MODE_SUM) {
+    hipLaunchKernelGGL((dl_gemm_kernel<MODE, FORM_ROWS>), g, blk, 0, s, a);
   }
 }
 
@@ -1156,17 +1394,17 @@ static hipError_t launch_kt(const GemmArgs& a0, int dt, bool vec, int cus, size_
   a.n_full = a.n_items;
   a.n_split = 0;
   a.ksplit = 1;
-  // The accumulator form needs every K-stage inside one example.
-  const int ks = dt == DT_BF16 ? KT<DT_BF16>::KS : KT<DT_F32>::KS;
-  const int sc = MODE == MODE_NORM ? SC_NONE : (a.T % ks == 0 ? SC_ACC : SC_STAGE);
-  // Example groups and the gradient store exist only on the direct-load kernel.
-  const bool dl = dt == DT_BF16 && vec && a.T % DL_BK == 0;
-  if (MODE == MODE_NORM && (a.eg < 1 || a.eg > NG_MAX || ((a.eg > 1 || a.store) && !dl)))
+  // Example groups exist only on the bf16 kernel, the gradient store only on
+  // its direct loads of whole stages.
+  if (MODE == MODE_NORM && (a.eg < 1 || a.eg > NG_MAX || (a.eg > 1 && dt != DT_BF16) ||
+                            (a.store && !(dt == DT_BF16 && vec && a.T % DL_BK == 0))))
     return hipErrorInvalidValue;
   if (MODE == MODE_SUM && a.store) return hipErrorInvalidValue;
-  if (dt == DT_BF16 && vec && a.T % DL_BK == 0 && (MODE == MODE_NORM || a.B <= DL_MAXB)) {
+  if (dt == DT_BF16) {
+    const int form = a.big ? (int)FORM_BIG
+                           : (MODE == MODE_NORM ? norm_form(vec, a.T) : sum_form(vec, a.T, a.B));
     uint32_t grid = a.n_items;
-    if (MODE == MODE_SUM && a.part != nullptr) {
+    if (MODE == MODE_SUM && a.part != nullptr && dl_sum_applies(dt, vec, a.T, a.B)) {
       const TailSplit t = tail_split(a.n_items, (int)((int64_t)a.B * a.T / DL_BK), cus);
       if (t.n_split > 0 && (size_t)t.n_split * t.ks * SPLIT_TILE_BYTES <= part_bytes) {
         a.n_full = t.n_full;
@@ -1175,23 +1413,15 @@ static hipError_t launch_kt(const GemmArgs& a0, int dt, bool vec, int cus, size_
         grid = t.n_full + t.n_split * (uint32_t)t.ks;
       }
     }
-    if (a.big)
-      hipLaunchKernelGGL((dl_gemm_kernel<MODE, true>), dim3(grid), dim3(GM_THREADS), 0, s, a);
-    else
-      hipLaunchKernelGGL((dl_gemm_kernel<MODE, false>), dim3(grid), dim3(GM_THREADS), 0, s, a);
+    launch_dl<MODE>(a, form, grid, s);
     if (a.n_split > 0) {
       hipLaunchKernelGGL(split_fixup_kernel, dim3(a.n_split * (GM_BM * GM_BN / 4 / 256)),
                          dim3(256), 0, s, a);
     }
     return hipGetLastError();
   }
-  if (dt == DT_BF16) {
-    if (vec) launch_sc<DT_BF16, true, MODE>(a, sc, s);
-    else launch_sc<DT_BF16, false, MODE>(a, sc, s);
-  } else {
-    if (vec) launch_sc<DT_F32, true, MODE>(a, sc, s);
-    else launch_sc<DT_F32, false, MODE>(a, sc, s);
-  }
+  if (vec) launch_f32<true, MODE>(a, s);
+  else launch_f32<false, MODE>(a, s);
   return hipGetLastError();
 }
 

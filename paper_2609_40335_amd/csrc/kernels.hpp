@@ -155,10 +155,32 @@ struct GemmArgs {
 
 static_assert(sizeof(GemmArgs) <= 4096, "kernel arguments must stay within 4 KiB");
 
-// The bf16 direct-load clipped-sum kernel's conditions (16-byte rows, whole
-// 32-row stages per example, the factor table in LDS).
+// Forms of the bf16 GEMM's stages (32 rows each).
+//  PLAIN:  16-byte rows, T a multiple of 32, loaded straight into LDS.
+//  BIG:    the same with an operand of 4 GiB or more.
+//  RAGGED: 16-byte rows, any T: an example's last stage may be short; its
+//          missing rows read as zeros.
+//  STAGED: rows of any alignment, any T, loaded through registers.
+//  ROWS:   (clipped sum) stages run over the batch's rows without regard to
+//          examples, and X's rows are scaled while staged (c_i A rounds to
+//          bf16). For short examples, whose padding to whole stages would cost
+//          more: ROWS_NUM / ROWS_DEN is the measured ratio of a ROWS stage's
+//          time to a RAGGED one's.
+enum GemmForm { FORM_PLAIN = 0, FORM_BIG, FORM_RAGGED, FORM_STAGED, FORM_ROWS };
 constexpr int DL_SUM_BK = 32;
-constexpr int DL_SUM_MAXB = 4096;
+constexpr int DL_SUM_MAXB = 4096;  // clip factors held in LDS
+constexpr int ROWS_NUM = 3, ROWS_DEN = 2;
+inline int sum_form(bool vec, int T, int B) {
+  if (T % DL_SUM_BK == 0) return !vec ? FORM_STAGED : B <= DL_SUM_MAXB ? FORM_PLAIN : FORM_RAGGED;
+  const int64_t padded = (int64_t)((T + DL_SUM_BK - 1) / DL_SUM_BK) * DL_SUM_BK;
+  if (padded * ROWS_DEN > (int64_t)T * ROWS_NUM) return FORM_ROWS;
+  return vec ? FORM_RAGGED : FORM_STAGED;
+}
+inline int norm_form(bool vec, int T) {
+  return !vec ? FORM_STAGED : T % DL_SUM_BK == 0 ? FORM_PLAIN : FORM_RAGGED;
+}
+// The launches whose operands may span 4 GiB or more, and whose tail may be
+// split.
 inline bool dl_sum_applies(int dt, bool vec, int T, int B) {
   return dt == DT_BF16 && vec && T % DL_SUM_BK == 0 && B <= DL_SUM_MAXB;
 }

@@ -63,3 +63,46 @@ def test_norms_of_every_form(shape, rows, dtype):
     bw = G.double().sum(1)
     torch.testing.assert_close(bias.double(), bw, rtol=1e-4, atol=1e-5 * float(bw.abs().max()) + 1e-6)
     torch.testing.assert_close(n2.double(), want + bw.square().sum(1), rtol=1e-5, atol=0)
+
+
+def factors(B):
+    c = torch.linspace(0.05, 1.0, B, device="cuda")
+    if B > 2:
+        c[1] = 0.0   # an example that is left out
+    return c
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("rows", ["aligned", "odd"])
+@pytest.mark.parametrize("shape", SHAPES + [(300, 3, 24, 40), (5000, 1, 16, 16), (4100, 32, 8, 24)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_clipped_sums_of_every_form(shape, rows, dtype):
+    from paper_2609_40335_amd import dpghost as dp
+    B, T, di, do = shape
+    up = (lambda w: (w + 7) // 8 * 8) if rows == "aligned" else (lambda w: w + (1 - w % 2))
+    off = 0 if rows == "aligned" else 3
+    A, G, g = operands(2, B, T, di, do, dtype, up(di), up(do), off)
+    c = factors(B)
+    if B > 2:
+        A[1] = float("inf")   # left out, whatever it holds
+    Ac = torch.where(c.view(B, 1, 1) == 0, 0.0, A.double()) * c.double().view(B, 1, 1)
+    want = torch.einsum("km,kn->mn", Ac.reshape(B * T, di), G.double().reshape(B * T, do))
+    bound = 1e-5 if dtype == torch.float32 or 2 * (-T % 32) <= T else 5e-3
+    prior = torch.randn(di, do, generator=g, device="cuda")
+    for transpose in (False, True):
+        w = want.t() if transpose else want
+        out = torch.full(tuple(w.shape), float("nan"), device="cuda")
+        dp.dp_clipped_grad_sum(A, G, c, out, transpose_out=transpose)
+        rel = float((out.double() - w).norm() / w.norm())
+        assert rel < bound, (transpose, rel)
+        out.copy_(prior.t() if transpose else prior)
+        dp.dp_clipped_grad_sum(A, G, c, out, transpose_out=transpose, accumulate=True)
+        w2 = w + (prior.t() if transpose else prior).double()
+        assert float((out.double() - w2).norm() / w2.norm()) < bound
+    # the same with the noise fused, against the sum and the noise apart
+    grp = dp.LinearGroup([(A, G)], [torch.full((di, do), float("nan"), device="cuda")])
+    grp.clipped_sum_noised(c, [5], 0.5, 1.0, 3, 11, 2)
+    z = torch.zeros(di, do, device="cuda")
+    dp.dp_add_noise(z, 0.5, 1.0, 0, 11, 5, 2)
+    w3 = (want + z.double()) / 3
+    assert float((grp._outs[0].double() - w3).norm() / w3.norm()) < bound
