@@ -106,6 +106,38 @@ __device__ __forceinline__ f32x16 mfma32_f32(float a, float b, const f32x16& c) 
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
+// fp32 products on the bf16 matrix cores: a value is cut exactly into three bf16
+// planes, x = x0 + x1 + x2: x0 its upper 16 bits (cut off, so that nothing
+// overflows), x1 the rest rounded to nearest, x2 what is left (8 bits at most).
+// |x1| <= 2^-7 |x|, |x2| <= 2^-16 |x|, and the sign of x2 is that of a
+// rounding error. A product is the sum of the SPLIT_TERMS plane products
+// below, smallest first; the ones left out (x1 y2, x2 y1, x2 y2) are at most
+// 2^-22 and about 2^-26 of it on average, with signs as random as a rounding's.
+// Values below 2^-102 lose low bits in the planes (bf16 ends at 2^-126), and an
+// infinity's planes hold NaN (inf - inf), so that it gives NaN.
+constexpr int SPLIT_TERMS = 6;
+__device__ __forceinline__ constexpr int split_a(int t) {
+  return t == 0 ? 0 : t == 1 ? 2 : t == 2 ? 1 : t == 3 ? 0 : t == 4 ? 1 : 0;
+}
+__device__ __forceinline__ constexpr int split_b(int t) {
+  return t == 0 ? 2 : t == 1 ? 0 : t == 2 ? 1 : t == 3 ? 1 : 0;
+}
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+// Two values' planes, two bf16 per dword.
+struct Split2 { uint32_t p[3]; };
+__device__ __forceinline__ Split2 split_f32(float a, float b) {
+  constexpr uint32_t HIGH = 0x07060302u;  // the upper halves of two dwords
+  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+  Split2 s;
+  s.p[0] = __builtin_amdgcn_perm(ub, ua, HIGH);
+  const float ra = a - __uint_as_float(ua & 0xFFFF0000u), rb = b - __uint_as_float(ub & 0xFFFF0000u);
+  s.p[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
+  const float la = ra - __uint_as_float(s.p[1] << 16), lb = rb - __uint_as_float(s.p[1] & 0xFFFF0000u);
+  s.p[2] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), HIGH);
+  return s;
+}
+
 // Buffer resources: loads through them need no bounds branches, because the
 // hardware returns 0 for any dword at or past num_records bytes.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;

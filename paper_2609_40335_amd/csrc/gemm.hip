@@ -18,29 +18,16 @@
 // when T + 1 exceeds about R * 2 d_in d_out / (d_in + d_out), R the measured
 // ratio of the two kernels' throughputs (about 0.4 to 0.5).
 //
-// Kernels. dl_gemm_kernel (bf16, 16-byte rows, whole 32-row stages per
-// example: the clipped sum and the direct norm) loads rows straight into LDS
-// and transposes on the way out of LDS; split_fixup_kernel finishes the tiles
-// of its split tail. The general kernel kt_gemm_kernel (fp32, unaligned
-// strides, any T) stages through registers:
-//
-// MFMA wants 8 consecutive k per lane, but both operands are contiguous along
-// M/N. Each staging thread loads an 8(k) x 8(m) block with 16-byte buffer
-// loads, scales it (X only: exact widening, fp32 multiply,
-// v_cvt_pk_bf16_f32 rounding) and transposes it in registers into 8
-// k-contiguous chunks written to LDS. Waves 0-3 stage X, waves 4-7 stage Y.
-// Tile 256x256, 64 (bf16) or 32 (fp32) k per stage, LDS double-buffered with
-// one barrier per stage; each of the 8 waves owns a 128x64 quadrant of 4x2
-// 32x32 MFMA blocks, so two waves share every SIMD.
+// Kernels. dl_gemm_kernel (bf16: the clipped sum and the direct norm) stages
+// rows in LDS and transposes on the way out of LDS; split_fixup_kernel
+// finishes the tiles of its split tail. split_gemm_kernel (fp32) cuts its operands into
+// three bf16 planes while staging them and multiplies on the bf16 matrix cores.
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace dpg {
 
 constexpr int GM_THREADS = 512;
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 enum { MODE_SUM = 0, MODE_NORM = 1 };
 
@@ -49,112 +36,6 @@ enum { MODE_SUM = 0, MODE_NORM = 1 };
 __device__ __forceinline__ uint32_t scale_bf16x2(uint32_t w, float s) {
   f32x2 v = {__uint_as_float(w << 16) * s, __uint_as_float(w & 0xFFFF0000u) * s};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-template <int DT>
-struct KT {
-  static constexpr int RPT = (DT == DT_BF16) ? 8 : 4;  // k rows per thread per stage
-  static constexpr int KS = 8 * RPT;                   // k rows per stage
-  static constexpr int ES = (DT == DT_BF16) ? 2 : 4;
-  static constexpr int EPC = 16 / ES;                  // elements per 16-byte chunk
-  static constexpr int CPR = 8 / RPT;                  // chunks per 8-column segment
-};
-
-// This thread's block of one operand: rows r0 .. r0+RPT-1 (r0 relative to
-// the stage) at columns col .. col+7. voff is this lane's byte offset of
-// (r0, col) and soff the wave-uniform byte offset of the stage's first row.
-// ROWMASK: rows at or past `rows_left` (counted from the stage start) read
-// as zero (they belong to the next example).
-template <int DT, bool VEC, bool MASKC, bool ROWMASK>
-__device__ __forceinline__ void load_block(rsrc_t r, uint32_t voff, uint32_t soff,
-                                           uint32_t ld_bytes, int r0, int64_t rows_left,
-                                           int64_t col, int64_t ncol, u32x4 (&raw)[8]) {
-  using P = KT<DT>;
-#pragma unroll
-  for (int j = 0; j < P::RPT; ++j) {
-#pragma unroll
-    for (int h = 0; h < P::CPR; ++h) {
-      u32x4 v = buf_chunk<DT, VEC, MASKC>(r, voff + h * 16, soff + j * ld_bytes,
-                                          col + h * P::EPC, ncol);
-      if (ROWMASK && r0 + j >= rows_left) v = u32x4{0u, 0u, 0u, 0u};
-      raw[j * P::CPR + h] = v;
-    }
-  }
-}
-
-// Scales row j of the block by s[j], transposes it into 8 column chunks of
-// RPT consecutive k, and writes them to LDS rows m_row0 .. m_row0+7, chunk kg.
-template <int DT, bool SCALE>
-__device__ __forceinline__ void store_block_t(u32x4* lds, u32x4 (&raw)[8], const float (&s)[8],
-                                              int m_row0, int kg) {
-  if constexpr (DT == DT_BF16) {
-    if (SCALE) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int p = 0; p < 4; ++p) raw[j][p] = scale_bf16x2(raw[j][p], s[j]);
-    }
-#pragma unroll
-    for (int mm = 0; mm < 8; ++mm) {
-      const int p = mm >> 1;
-      const uint32_t sel = (mm & 1) ? 0x07060302u : 0x05040100u;
-      u32x4 o;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        o[q] = __builtin_amdgcn_perm(raw[2 * q + 1][p], raw[2 * q][p], sel);
-      const int r = m_row0 + mm;
-      lds[r * 8 + swz(r, kg)] = o;
-    }
-  } else {
-#pragma unroll
-    for (int mm = 0; mm < 8; ++mm) {
-      const int h = mm >> 2, e = mm & 3;
-      u32x4 o;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float v = __uint_as_float(raw[j * 2 + h][e]);
-        if (SCALE) v *= s[j];
-        o[j] = __float_as_uint(v);
-      }
-      const int r = m_row0 + mm;
-      lds[r * 8 + swz(r, kg)] = o;
-    }
-  }
-}
-
-// One LDS stage into this wave's 4x2 blocks: X rows wm*128 + i*32, Y rows
-// wn*64 + j*32. Lane l supplies row l%32 and 16-byte chunk 2*ks + l/32.
-template <int DT>
-__device__ __forceinline__ void tile_mfma(const u32x4* __restrict__ Xs, const u32x4* __restrict__ Ys,
-                                          f32x16 (&acc)[4][2], int wm, int wn, int lane) {
-  const int r32 = lane & 31, half = lane >> 5;
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    const int c = 2 * ks + half;
-    u32x4 xa[4], yb[2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int rx = wm * 128 + i * 32 + r32;
-      xa[i] = Xs[rx * 8 + swz(rx, c)];
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int ry = wn * 64 + j * 32 + r32;
-      yb[j] = Ys[ry * 8 + swz(ry, c)];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        if constexpr (DT == DT_BF16) {
-          acc[i][j] = mfma32_bf16(xa[i], yb[j], acc[i][j]);
-        } else {
-#pragma unroll
-          for (int m = 0; m < 4; ++m)
-            acc[i][j] = mfma32_f32(__uint_as_float(xa[i][m]), __uint_as_float(yb[j][m]), acc[i][j]);
-        }
-      }
-  }
 }
 
 // Tile (mt, nt) of work item rel within a layer: the direction with fewer
@@ -434,22 +315,45 @@ __global__ __launch_bounds__(256) void split_fixup_kernel(GemmArgs args) {
   }
 }
 
-// Scaling of the clipped sum: SC_NONE (direct norm), SC_STAGE (rows scaled
-// while staged, any T; rows of examples with c = 0 zeroed in both operands),
-// SC_ACC (every stage lies inside one example, so the fp32 accumulators are
-// rescaled by c_prev / c_next at example boundaries and by the last factor at
-// the end; examples with c = 0 are skipped). Either way an example with
-// c = 0 contributes nothing, even where its rows hold inf or NaN.
-enum { SC_NONE = 0, SC_STAGE = 1, SC_ACC = 2 };
+// The fp32 clipped sum and direct norm: split_gemm_kernel. Every fp32 operand
+// is cut exactly into three bf16 planes (split_f32 in common.hpp), and a
+// product becomes six bf16 ones, the planes' products down to 2^-18 of it;
+// the dropped ones are below 2^-25 of it, like the rounding of an fp32
+// product. Six 32x32x16 bf16 MFMAs take 192 cycles where the eight fp32
+// 32x32x2 ones for the same 16 k take 512. The clipped sums of DistilGPT2 at
+// B = 24, T = 128, V = 50257 unpadded (498 GFLOP): 5171 us on the fp32 MFMAs
+// (96 TFLOP/s of the 157 they peak at, 154 in a large library product), 2551
+// us here (195 TFLOP/s, 1.17 PFLOP/s in bf16 terms), with an error against
+// fp64 of 7.7e-7 where the fp32 MFMAs gave 9.3e-7.
+//
+// Tile 256x256, 16 k per stage, 8 waves of 128x64 as in the bf16 kernel.
+// Waves 0-3 stage X, waves 4-7 Y: a wave takes 8 k rows and 128 columns, a
+// lane two neighbouring columns (8 bytes per row, so rows need 4-byte
+// alignment only), converts them after the load and writes a 16-byte chunk of 8
+// consecutive k per column and plane. (A stage of 32 k in three planes would
+// not fit LDS twice.) The conversion is about 6 VALU instructions per
+// element, once per tile and stage; the X waves convert before their MFMAs and
+// the Y waves after theirs, so that a SIMD's two waves (one of each) keep its
+// matrix core busy meanwhile. LDS is double-buffered, one barrier per stage;
+// the loads of stage s + 2 are in flight while stage s is multiplied.
+constexpr int SP_BK = 16;
+constexpr int SP_PLANE = 2 * GM_BM;         // 16-byte chunks of one plane: two k halves
+constexpr int SP_OP = 3 * SP_PLANE;         // of one operand
+constexpr int SP_STAGE = 2 * SP_OP;         // of one stage
+static_assert((GM_THREADS / WAVE) * 32 * EP_LD * 4 <= 2 * SP_STAGE * 16, "epilogue slices fit");
 
-template <int DT, bool VEC, int MODE, int SC>
-__global__ __launch_bounds__(GM_THREADS) void kt_gemm_kernel(GemmArgs args) {
+// Chunk of column m within a half plane: even columns first, odd ones behind
+// them with their 8-chunk groups swapped in pairs, so that both the writes
+// (a lane's even, then its odd column) and the reads of 32 consecutive columns
+// touch all banks evenly.
+__device__ __forceinline__ int sp_slot(int m) { return ((m >> 1) ^ ((m & 1) << 3)) + (m & 1) * (GM_BM / 2); }
+
+template <int MODE>
+__global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
   // Index the layer table in place in the kernel-argument segment.
   const GemmArgs& a = *(const GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   (void)args;
-  using P = KT<DT>;
-  __shared__ u32x4 Xs[2][GM_BM * 8];
-  __shared__ u32x4 Ys[2][GM_BN * 8];
+  __shared__ __attribute__((aligned(1024))) u32x4 lds[2 * SP_STAGE];
   __shared__ float red[GM_THREADS / WAVE];
 
   const uint32_t item = xcd_remap(blockIdx.x, gridDim.x);
@@ -457,167 +361,169 @@ __global__ __launch_bounds__(GM_THREADS) void kt_gemm_kernel(GemmArgs args) {
   const int l = wave_find(item, ln < a.n_layers ? a.L[ln].tile_begin : 0u, a.n_layers);
   const GemmLayer& L = a.L[l];
   uint32_t rel = item - L.tile_begin;
-  const uint32_t ntile = (uint32_t)L.tm * (uint32_t)L.tn;
-  const int64_t K = (int64_t)a.B * a.T;
   int b = 0;
-  int64_t k_begin = 0, k_end = K;
   if (MODE == MODE_NORM) {
+    const uint32_t ntile = (uint32_t)L.tm * (uint32_t)L.tn;
     b = (int)(rel / ntile);
     rel -= (uint32_t)b * ntile;
-    k_begin = (int64_t)b * a.T;
-    k_end = k_begin + a.T;
   }
   int mt, nt;
   tile_of(L, rel, mt, nt);
   const int64_t m0 = (int64_t)mt * GM_BM;
   const int64_t n0 = (int64_t)nt * GM_BN;
-
-  // The wave index goes through readfirstlane so that everything derived
-  // from it (staging role, buffer resource) is known to be wave-uniform.
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w & 1, wn = w >> 1;
-  // staging role: waves 0..3 stage X, waves 4..7 stage Y
-  const bool stage_x = w < 4;
-  const int st = tid & 255, kg = st >> 5, mg = st & 31;
-  const uint32_t ld_bytes = (uint32_t)((stage_x ? L.ldx : L.ldy) * P::ES);
-  const rsrc_t rsrc = make_rsrc(stage_x ? L.X : L.Y, (uint64_t)K * ld_bytes);
-  const int64_t col = (stage_x ? m0 : n0) + mg * 8;
-  const int64_t ncol = stage_x ? L.M : L.N;
-  const int r0 = kg * P::RPT;                       // this thread's first row in a stage
-  const uint32_t voff = (uint32_t)(r0 * ld_bytes + col * P::ES);
+
+  // Staging: rows 8 kh .. 8 kh + 7 of a stage, columns 128 mh + 2 lane, + 1.
+  // The descriptor spans the rows summed over (the batch, or one example);
+  // rows past them are pointed at its end and read as zeros. Columns past M/N
+  // read padding or the next row and only reach outputs that are left out.
+  const bool load_x = w < 4;
+  const int kh = (w & 3) >> 1, mh = w & 1;
+  const int64_t ld = load_x ? L.ldx : L.ldy;
+  const uint32_t ld_bytes = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ld * 4));
+  const int rows = MODE == MODE_NORM ? a.T : a.B * a.T;
+  const char* base = (const char*)(load_x ? L.X : L.Y) + (MODE == MODE_NORM ? (int64_t)b * a.T * ld * 4 : 0);
+  const rsrc_t rsrc = make_rsrc(base, (uint64_t)rows * ld_bytes);
+  const uint32_t voff = (uint32_t)(((load_x ? m0 : n0) + mh * 128 + 2 * lane) * 4);
+  const int slot0 = mh * 64 + lane;
+  u32x4* const wr = lds + (load_x ? 0 : SP_OP) + kh * GM_BM;
+  const int nS = (rows + SP_BK - 1) / SP_BK;
+
+  // Clip factors: row j of this wave's 8 rows of the next stage to load lies
+  // in example e_ld + (r_ld + j) / T; lane j fetches its factor.
+  // x / T = hi32(x * rcpT) for x < T + 8 (T <= 65536).
+  const int nT = __builtin_amdgcn_readfirstlane(a.T), nB = __builtin_amdgcn_readfirstlane(a.B);
+  const uint32_t rcpT = 0xFFFFFFFFu / (uint32_t)nT + 1u;
+  auto over_T = [&](int x) { return nT == 1 ? x : (int)__umulhi((uint32_t)x, rcpT); };
+  int e_ld = (kh * 8) / nT, r_ld = kh * 8 - e_ld * nT;
+  float cv = 1.f;   // factor of row lane % 8 of the loaded stage
+
+  u32x2 raw[8];
+  int row_ld = kh * 8;
+  auto load = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      raw[j] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
+                   rsrc, voff, (uint32_t)min(row_ld + j, rows) * ld_bytes, 0));
+    row_ld += SP_BK;
+    if constexpr (MODE == MODE_SUM) {
+      cv = a.c[min(e_ld + over_T(r_ld + (lane & 7)), nB - 1)];
+      r_ld += SP_BK;
+      const int de = __builtin_amdgcn_readfirstlane(r_ld < nT ? 0 : r_ld / nT);
+      e_ld += de;
+      r_ld -= de * nT;
+    }
+  };
+  // The loaded stage, scaled and cut, into LDS buffer `buf`.
+  auto convert = [&](int buf) __attribute__((always_inline)) {
+    u32x4* const dst = wr + buf * SP_STAGE;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      u32x4 p0, p1, p2;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float x[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int j = 2 * k + h;
+          x[h] = __uint_as_float(raw[j][q]);
+          if constexpr (MODE == MODE_SUM) {
+            // An example with c = 0 (a non-finite norm) is left out of the sum:
+            // its rows are zeroed in both operands (0 * inf would be NaN).
+            const float c = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cv), j));
+            x[h] *= load_x ? c : 1.f;
+            x[h] = __uint_as_float(__float_as_uint(x[h]) & (c == 0.f ? 0u : 0xFFFFFFFFu));
+          }
+        }
+        const Split2 sp = split_f32(x[0], x[1]);
+        p0[k] = sp.p[0];
+        p1[k] = sp.p[1];
+        p2[k] = sp.p[2];
+      }
+      const int at = q == 0 ? slot0 : GM_BM / 2 + (slot0 ^ 8);
+      dst[at] = p0;
+      dst[at + SP_PLANE] = p1;
+      dst[at + 2 * SP_PLANE] = p2;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
   f32x16 acc[4][2];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
+  const int r32 = lane & 31, half = lane >> 5;
+  const u32x4* const rd_x = lds + half * GM_BM + wm * 64 + sp_slot(r32);
+  const u32x4* const rd_y = lds + SP_OP + half * GM_BM + wn * 32 + sp_slot(r32);
+  auto compute = [&](int buf) __attribute__((always_inline)) {
+    // The next block row's fragments are read while this one's are multiplied.
+    // Fences bound how far the reads move up (all at once, they spill).
+    const u32x4* const bx = rd_x + buf * SP_STAGE;
+    const u32x4* const by = rd_y + buf * SP_STAGE;
+    u32x4 y[2][3], x[2][3];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  const int nS = (int)((k_end - k_begin + P::KS - 1) / P::KS);
-  const double invT = 1.0 / (double)a.T;
-  float sc[8];
+    for (int p = 0; p < 3; ++p) {
+      x[0][p] = bx[p * SP_PLANE];
+      y[0][p] = by[p * SP_PLANE];
+      y[1][p] = by[p * SP_PLANE + 16];
+    }
 #pragma unroll
-  for (int j = 0; j < 8; ++j) sc[j] = 1.f;
-  // Issues the global loads of stage s into r; with SC_STAGE also fetches
-  // the clip factors of this thread's rows.
-  auto load = [&](int s, u32x4 (&r)[8]) {
-    const int64_t ks0 = k_begin + (int64_t)s * P::KS;   // first row of the stage
-    // Rows past the matrix read as zero through the buffer bounds; columns
-    // past M/N only feed output rows that are never stored, except in the
-    // direct norm, whose tile sum must not see them (nor the next example).
-    load_block<DT, VEC, MODE == MODE_NORM, MODE == MODE_NORM>(
-        rsrc, voff, (uint32_t)(ks0 * ld_bytes), ld_bytes, r0, k_end - ks0, col, ncol, r);
-    if (SC == SC_STAGE) {
+    for (int i = 0; i < 4; ++i) {
+      if (i < 3) {
 #pragma unroll
-      for (int j = 0; j < P::RPT; ++j) {
-        int64_t e = (int64_t)(((double)(ks0 + r0 + j) + 0.5) * invT);
-        e = e < a.B ? e : a.B - 1;
-        sc[j] = a.c[e];
-        // An example with c = 0 (a non-finite norm) is left out of the sum:
-        // its rows are zeroed in both operands (0 * inf would be NaN).
-        if (sc[j] == 0.f) {
-#pragma unroll
-          for (int h = 0; h < P::CPR; ++h) r[j * P::CPR + h] = u32x4{0u, 0u, 0u, 0u};
-        }
+        for (int p = 0; p < 3; ++p) x[(i + 1) & 1][p] = bx[p * SP_PLANE + (i + 1) * 16];
       }
+#pragma unroll
+      for (int t = 0; t < SPLIT_TERMS; ++t)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = mfma32_bf16(x[i & 1][split_a(t)], y[j][split_b(t)], acc[i][j]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-  };
-  auto stage = [&](int buf, u32x4 (&r)[8]) {
-    if (stage_x)
-      store_block_t<DT, SC == SC_STAGE>(Xs[buf], r, sc, mg * 8, kg);
-    else
-      store_block_t<DT, false>(Ys[buf], r, sc, mg * 8, kg);
   };
 
-  // SC_ACC bookkeeping (wave-uniform): factor of the accumulated examples.
-  // The factor of the next example is fetched one example ahead so that no
-  // stage waits on it.
-  const int spe = (SC == SC_ACC) ? a.T / P::KS : 1;  // stages per example
-  float c_acc = 0.f;                                  // 0: nothing accumulated yet
-  float c_next = (SC == SC_ACC) ? a.c[0] : 0.f;
-  bool skip = false;
-  auto compute = [&](int s, int buf) {
-    if constexpr (SC == SC_ACC) {
-      if (s % spe == 0) {
-        const int e = s / spe;
-        const float ce = c_next;
-        if (e + 1 < a.B) c_next = a.c[e + 1];
-        skip = !(ce != 0.f);
-        if (!skip) {
-          if (c_acc != 0.f) {
-            const float f = c_acc / ce;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-              for (int j = 0; j < 2; ++j) acc[i][j] *= f;
-          }
-          c_acc = ce;
-        }
-      }
-      if (skip) return;
+  load();
+  convert(0);
+  load();
+  __syncthreads();
+  for (int s = 0; s < nS; ++s) {
+    const int buf = s & 1;
+    const bool more = s + 1 < nS;
+    if (load_x && more) {
+      convert(buf ^ 1);
+      load();
     }
-    tile_mfma<DT>(Xs[buf], Ys[buf], acc, wm, wn, lane);
-  };
-
-  if constexpr (SC == SC_ACC) {
-    // Two register sets: the loads of stage s+2 are in flight while stage s
-    // is multiplied and stage s+1 is transposed into the other LDS buffer.
-    // The scheduling fences keep each phase's instructions in place so that
-    // the compiler does not hoist loads across phases (which costs registers).
-    u32x4 rA[8], rB[8];
-    load(0, rA);
-    if (nS > 1) load(1, rB);
-    stage(0, rA);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(buf);
+    __builtin_amdgcn_sched_barrier(0);
+    if (!load_x && more) {
+      convert(buf ^ 1);
+      load();
+    }
     __syncthreads();
-    for (int s = 0; s < nS; s += 2) {
-      if (s + 2 < nS) load(s + 2, rA);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(s, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (s + 1 < nS) stage(1, rB);
-      __syncthreads();
-      if (s + 1 >= nS) break;
-      if (s + 3 < nS) load(s + 3, rB);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(s + 1, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (s + 2 < nS) stage(0, rA);
-      __syncthreads();
-    }
-  } else {
-    // One register set (these variants need more registers per stage): the
-    // loads of stage s+1 are in flight while stage s is multiplied.
-    u32x4 rA[8];
-    load(0, rA);
-    stage(0, rA);
-    __syncthreads();
-    for (int s = 0; s < nS; ++s) {
-      const int buf = s & 1;
-      if (s + 1 < nS) load(s + 1, rA);
-      compute(s, buf);
-      if (s + 1 < nS) stage(buf ^ 1, rA);
-      __syncthreads();
-    }
-  }
-  if constexpr (SC == SC_ACC) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] *= c_acc;
   }
 
   if constexpr (MODE == MODE_SUM) {
     // The host orders every launch so that the kernel's rows are the output's.
-    store_tile_rows(a, L, m0, n0, wm, wn, lane, acc, (float*)&Xs[0][0] + w * 32 * EP_LD);
+    store_tile_rows(a, L, m0, n0, wm, wn, lane, acc, (float*)lds + w * 32 * EP_LD);
   } else {
+    const int lim_m = (int)(L.M - m0) - (wm * 128 + (lane >> 5) * 4);
+    const int lim_n = (int)(L.N - n0) - (wn * 64 + (lane & 31));
     float part = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < 2; ++j) {
+        const bool nin = j * 32 < lim_n;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) part += acc[i][j][e] * acc[i][j][e];
+        for (int e = 0; e < 16; ++e) {
+          const float v = acc[i][j][e];
+          part += (nin && i * 32 + (e >> 2) * 8 + (e & 3) < lim_m) ? v * v : 0.f;
+        }
+      }
     part = wave_sum(part);
     if (lane == 0) red[w] = part;
     __syncthreads();
@@ -1356,20 +1262,6 @@ hipError_t launch_store_sum(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool VEC, int MODE>
-static void launch_f32(const GemmArgs& a, hipStream_t s) {
-  const dim3 g(a.n_items), blk(GM_THREADS);
-  if constexpr (MODE == MODE_NORM) {
-    hipLaunchKernelGGL((kt_gemm_kernel<DT_F32, VEC, MODE, SC_NONE>), g, blk, 0, s, a);
-  } else {
-    // The accumulator form needs every K-stage inside one example.
-    if (a.T % KT<DT_F32>::KS == 0)
-      hipLaunchKernelGGL((kt_gemm_kernel<DT_F32, VEC, MODE, SC_ACC>), g, blk, 0, s, a);
-    else
-      hipLaunchKernelGGL((kt_gemm_kernel<DT_F32, VEC, MODE, SC_STAGE>), g, blk, 0, s, a);
-  }
-}
-
 template <int MODE>
 static void launch_dl(const GemmArgs& a, int form, uint32_t grid, hipStream_t s) {
   const dim3 g(grid), blk(GM_THREADS);
@@ -1420,8 +1312,7 @@ static hipError_t launch_kt(const GemmArgs& a0, int dt, bool vec, int cus, size_
     }
     return hipGetLastError();
   }
-  if (vec) launch_f32<true, MODE>(a, s);
-  else launch_f32<false, MODE>(a, s);
+  hipLaunchKernelGGL((split_gemm_kernel<MODE>), dim3(a.n_items), dim3(GM_THREADS), 0, s, a);
   return hipGetLastError();
 }
 

@@ -106,3 +106,27 @@ def test_clipped_sums_of_every_form(shape, rows, dtype):
     dp.dp_add_noise(z, 0.5, 1.0, 0, 11, 5, 2)
     w3 = (want + z.double()) / 3
     assert float((grp._outs[0].double() - w3).norm() / w3.norm()) < bound
+
+
+@pytest.mark.parametrize("span", [0, 30], ids=["ordinary", "wide"])
+def test_fp32_products_keep_their_bits(span):
+    """One token, so that every output is one product of two fp32 values, over
+    2 * span + 1 binary orders. A product of values cut into bf16 planes leaves out
+    terms of at most 2^-22 of it (a plane kept too few would show as 2^-16);
+    the norm is a product of two such sums over 300 and 260 features."""
+    from paper_2609_40335_amd import dpghost as dp
+    g = torch.Generator(device="cuda").manual_seed(9)
+
+    def values(w):
+        x = torch.randn(1, 1, w, generator=g, device="cuda")
+        return x * torch.exp2(torch.randint(-span, span + 1, (1, 1, w), generator=g, device="cuda").float())
+
+    A, G = values(300), values(260)
+    out = torch.zeros(300, 260, device="cuda")
+    dp.dp_clipped_grad_sum(A, G, torch.ones(1, device="cuda"), out)
+    want = A.double().view(-1, 1) * G.double().view(1, -1)
+    assert float(((out.double() - want) / want).abs().max()) <= 2.0 ** -21
+    for algo in (dp.DP_NORM_GRAM, dp.DP_NORM_DIRECT):
+        n2 = torch.zeros(1, device="cuda")
+        dp.dp_ghost_norm_linear(A, G, n2, algo=algo)
+        assert abs(float(n2) / float(want.square().sum()) - 1) <= 2.0 ** -19
