@@ -391,22 +391,25 @@ std::vector<std::pair<bool, std::vector<const GemmEntry*>>> gemm_launches(
 }
 
 // Bytes of partial tiles the split tail of a clipped-sum plan needs (the
-// largest over its launches, which run one after another).
-size_t sum_split_bytes(const std::vector<GemmEntry>& entries, int B, int T, dp_dtype_t dt) {
+// largest over its launches, which run one after another). every: for every
+// form of operand, or only those that could be split first (bf16, 16-byte rows,
+// whole 32-row stages), whose workspace query keeps its value.
+size_t sum_split_bytes(const std::vector<GemmEntry>& entries, int B, int T, dp_dtype_t dt,
+                       bool every) {
   size_t need = 0;
   for (const auto& [vec, sel] : gemm_launches(entries)) {
-    if (!dpg::dl_sum_applies(kdt(dt), vec, T, B)) continue;
+    if (!every && !dpg::dl_sum_applies(kdt(dt), vec, T, B)) continue;
     uint64_t tiles = 0;
     for (const GemmEntry* e : sel) tiles += (uint64_t)e->tm * e->tn;
-    const dpg::TailSplit t = dpg::tail_split(tiles, (int)((int64_t)B * T / dpg::DL_SUM_BK),
-                                             device_cus());
+    const dpg::TailSplit t =
+        dpg::tail_split(tiles, dpg::sum_stages(kdt(dt), vec, T, B), device_cus());
     need = std::max(need, (size_t)t.n_split * t.ks * dpg::SPLIT_TILE_BYTES);
   }
   return need;
 }
 
 // mode 0: clipped sum (c, out); mode 1: direct norm (ws, slots). A clipped sum
-// given `part` (part_bytes) splits the tail of its direct-load launches.
+// given `part` (part_bytes) splits the tail of its launches.
 dp_status_t run_gemm(const std::vector<GemmEntry>& entries, int mode, int B, int T, dp_dtype_t dt,
                      const float* c, float* ws, int64_t slots, int transpose, const NoiseCfg& nz,
                      hipStream_t s, float* part = nullptr, size_t part_bytes = 0,
@@ -931,13 +934,15 @@ size_t dp_clipped_grad_sum_workspace(int B, int T, int d_out, int with_ids) {
   return es_layout((int64_t)B * T, d_out).total;
 }
 
-dp_status_t dp_clipped_grad_sum_grouped(const dp_linear_t* layers, float* const* outs,
-                                        int n_layers, const float* c, int B, int T,
-                                        dp_dtype_t dt, int transpose_out, int accumulate,
-                                        void* stream) {
+dp_status_t dp_clipped_grad_sum_grouped_ws(const dp_linear_t* layers, float* const* outs,
+                                           int n_layers, const float* c, int B, int T,
+                                           dp_dtype_t dt, int transpose_out, int accumulate,
+                                           void* workspace, size_t workspace_bytes,
+                                           void* stream) {
   dp_status_t st = check_layers(layers, n_layers, B, T, dt);
   if (st != DP_OK) return st;
   if (!outs || !c) return fail(DP_EINVAL, "outs or c is NULL");
+  if (workspace_bytes && !workspace) return fail(DP_EINVAL, "workspace is NULL");
   if ((int64_t)B * T > (int64_t(1) << 40)) return fail(DP_EUNSUPPORTED, "B*T too large");
   std::vector<GemmEntry> entries;
   for (int i = 0; i < n_layers; ++i) {
@@ -945,7 +950,16 @@ dp_status_t dp_clipped_grad_sum_grouped(const dp_linear_t* layers, float* const*
     plan_sum(layers[i], transpose_out, dt, outs[i], entries);
     entries.back().acc = accumulate ? 1 : 0;
   }
-  return run_gemm(entries, 0, B, T, dt, c, nullptr, 0, 0, NoiseCfg{}, as_stream(stream));
+  return run_gemm(entries, 0, B, T, dt, c, nullptr, 0, 0, NoiseCfg{}, as_stream(stream),
+                  static_cast<float*>(workspace), workspace ? workspace_bytes : 0);
+}
+
+dp_status_t dp_clipped_grad_sum_grouped(const dp_linear_t* layers, float* const* outs,
+                                        int n_layers, const float* c, int B, int T,
+                                        dp_dtype_t dt, int transpose_out, int accumulate,
+                                        void* stream) {
+  return dp_clipped_grad_sum_grouped_ws(layers, outs, n_layers, c, B, T, dt, transpose_out,
+                                        accumulate, nullptr, 0, stream);
 }
 
 static dp_status_t noised_sum_plan(const dp_linear_t* layers, float* const* outs,
@@ -966,14 +980,24 @@ static dp_status_t noised_sum_plan(const dp_linear_t* layers, float* const* outs
   return DP_OK;
 }
 
-size_t dp_clipped_grad_sum_noised_grouped_workspace(const dp_linear_t* layers, int n_layers,
-                                                    int B, int T, dp_dtype_t dt,
-                                                    int transpose_out) {
+static size_t split_workspace(const dp_linear_t* layers, int n_layers, int B, int T,
+                              dp_dtype_t dt, int transpose_out, bool every) {
   std::vector<GemmEntry> entries;
   if (noised_sum_plan(layers, nullptr, nullptr, nullptr, n_layers, B, T, dt, transpose_out,
                       entries) != DP_OK)
     return 0;
-  return align_up(sum_split_bytes(entries, B, T, dt));
+  return align_up(sum_split_bytes(entries, B, T, dt, every));
+}
+
+size_t dp_clipped_grad_sum_noised_grouped_workspace(const dp_linear_t* layers, int n_layers,
+                                                    int B, int T, dp_dtype_t dt,
+                                                    int transpose_out) {
+  return split_workspace(layers, n_layers, B, T, dt, transpose_out, false);
+}
+
+size_t dp_clipped_grad_sum_split_workspace(const dp_linear_t* layers, int n_layers, int B, int T,
+                                           dp_dtype_t dt, int transpose_out) {
+  return split_workspace(layers, n_layers, B, T, dt, transpose_out, true);
 }
 
 dp_status_t dp_clipped_grad_sum_noised_grouped_ws(const dp_linear_t* layers, float* const* outs,
@@ -1215,8 +1239,8 @@ dp_status_t dp_clipped_grad_sum(const void* A, int64_t lda, const void* G, int64
                                 void* stream) {
   if (!ids) {
     dp_linear_t L{A, lda, d_in, G, ldg, d_out, DP_NORM_AUTO};
-    return dp_clipped_grad_sum_grouped(&L, &out, 1, c, B, T, dt, transpose_out, accumulate,
-                                       stream);
+    return dp_clipped_grad_sum_grouped_ws(&L, &out, 1, c, B, T, dt, transpose_out, accumulate,
+                                          workspace, workspace ? workspace_bytes : 0, stream);
   }
   // Embedding form: A = onehot(ids), d_in = V.
   if (A) return fail(DP_EINVAL, "pass either A or ids, not both");

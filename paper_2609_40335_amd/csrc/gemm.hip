@@ -336,7 +336,6 @@ __global__ __launch_bounds__(256) void split_fixup_kernel(GemmArgs args) {
 // the Y waves after theirs, so that a SIMD's two waves (one of each) keep its
 // matrix core busy meanwhile. LDS is double-buffered, one barrier per stage;
 // the loads of stage s + 2 are in flight while stage s is multiplied.
-constexpr int SP_BK = 16;
 constexpr int SP_PLANE = 2 * GM_BM;         // 16-byte chunks of one plane: two k halves
 constexpr int SP_OP = 3 * SP_PLANE;         // of one operand
 constexpr int SP_STAGE = 2 * SP_OP;         // of one stage
@@ -356,7 +355,16 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
   __shared__ __attribute__((aligned(1024))) u32x4 lds[2 * SP_STAGE];
   __shared__ float red[GM_THREADS / WAVE];
 
-  const uint32_t item = xcd_remap(blockIdx.x, gridDim.x);
+  // Whole tiles, then the K ranges of the split tail's (see dl_gemm_kernel).
+  uint32_t item;
+  int kc = -1;
+  if (MODE == MODE_NORM || blockIdx.x < a.n_full) {
+    item = xcd_remap(blockIdx.x, MODE == MODE_NORM ? gridDim.x : a.n_full);
+  } else {
+    const uint32_t j = blockIdx.x - a.n_full;
+    item = a.n_full + j / (uint32_t)a.ksplit;
+    kc = (int)(j - (j / (uint32_t)a.ksplit) * (uint32_t)a.ksplit);
+  }
   const int ln = (int)(threadIdx.x & (WAVE - 1));
   const int l = wave_find(item, ln < a.n_layers ? a.L[ln].tile_begin : 0u, a.n_layers);
   const GemmLayer& L = a.L[l];
@@ -389,7 +397,12 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
   const uint32_t voff = (uint32_t)(((load_x ? m0 : n0) + mh * 128 + 2 * lane) * 4);
   const int slot0 = mh * 64 + lane;
   u32x4* const wr = lds + (load_x ? 0 : SP_OP) + kh * GM_BM;
-  const int nS = (rows + SP_BK - 1) / SP_BK;
+  int s0 = 0, nS = (rows + SP_BK - 1) / SP_BK;  // stages s0 .. s0 + nS - 1
+  if (MODE == MODE_SUM && kc >= 0) {
+    const int per = (nS + a.ksplit - 1) / a.ksplit;
+    s0 = kc * per;
+    nS = s0 + per < nS ? per : (s0 < nS ? nS - s0 : 0);
+  }
 
   // Clip factors: row j of this wave's 8 rows of the next stage to load lies
   // in example e_ld + (r_ld + j) / T; lane j fetches its factor.
@@ -397,11 +410,11 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
   const int nT = __builtin_amdgcn_readfirstlane(a.T), nB = __builtin_amdgcn_readfirstlane(a.B);
   const uint32_t rcpT = 0xFFFFFFFFu / (uint32_t)nT + 1u;
   auto over_T = [&](int x) { return nT == 1 ? x : (int)__umulhi((uint32_t)x, rcpT); };
-  int e_ld = (kh * 8) / nT, r_ld = kh * 8 - e_ld * nT;
+  int row_ld = s0 * SP_BK + kh * 8;   // this wave's first row of the next stage to load
+  int e_ld = row_ld / nT, r_ld = row_ld - e_ld * nT;
   float cv = 1.f;   // factor of row lane % 8 of the loaded stage
 
   u32x2 raw[8];
-  int row_ld = kh * 8;
   auto load = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
@@ -507,8 +520,13 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
   }
 
   if constexpr (MODE == MODE_SUM) {
+    float* const slice = (float*)lds + w * 32 * EP_LD;
     // The host orders every launch so that the kernel's rows are the output's.
-    store_tile_rows(a, L, m0, n0, wm, wn, lane, acc, (float*)lds + w * 32 * EP_LD);
+    if (kc < 0)
+      store_tile_rows(a, L, m0, n0, wm, wn, lane, acc, slice);
+    else
+      store_partial(a.part + ((size_t)(item - a.n_full) * a.ksplit + kc) * (GM_BM * GM_BN), wm, wn,
+                    lane, acc, slice);
   } else {
     const int lim_m = (int)(L.M - m0) - (wm * 128 + (lane >> 5) * 4);
     const int lim_n = (int)(L.N - n0) - (wn * 64 + (lane & 31));
@@ -1292,27 +1310,27 @@ static hipError_t launch_kt(const GemmArgs& a0, int dt, bool vec, int cus, size_
                             (a.store && !(dt == DT_BF16 && vec && a.T % DL_BK == 0))))
     return hipErrorInvalidValue;
   if (MODE == MODE_SUM && a.store) return hipErrorInvalidValue;
+  uint32_t grid = a.n_items;
+  if (MODE == MODE_SUM && a.part != nullptr && ((uintptr_t)a.part & 15) == 0) {
+    const TailSplit t = tail_split(a.n_items, sum_stages(dt, vec, a.T, a.B), cus);
+    if (t.n_split > 0 && (size_t)t.n_split * t.ks * SPLIT_TILE_BYTES <= part_bytes) {
+      a.n_full = t.n_full;
+      a.n_split = t.n_split;
+      a.ksplit = t.ks;
+      grid = t.n_full + t.n_split * (uint32_t)t.ks;
+    }
+  }
   if (dt == DT_BF16) {
     const int form = a.big ? (int)FORM_BIG
                            : (MODE == MODE_NORM ? norm_form(vec, a.T) : sum_form(vec, a.T, a.B));
-    uint32_t grid = a.n_items;
-    if (MODE == MODE_SUM && a.part != nullptr && dl_sum_applies(dt, vec, a.T, a.B)) {
-      const TailSplit t = tail_split(a.n_items, (int)((int64_t)a.B * a.T / DL_BK), cus);
-      if (t.n_split > 0 && (size_t)t.n_split * t.ks * SPLIT_TILE_BYTES <= part_bytes) {
-        a.n_full = t.n_full;
-        a.n_split = t.n_split;
-        a.ksplit = t.ks;
-        grid = t.n_full + t.n_split * (uint32_t)t.ks;
-      }
-    }
     launch_dl<MODE>(a, form, grid, s);
-    if (a.n_split > 0) {
-      hipLaunchKernelGGL(split_fixup_kernel, dim3(a.n_split * (GM_BM * GM_BN / 4 / 256)),
-                         dim3(256), 0, s, a);
-    }
-    return hipGetLastError();
+  } else {
+    hipLaunchKernelGGL((split_gemm_kernel<MODE>), dim3(grid), dim3(GM_THREADS), 0, s, a);
   }
-  hipLaunchKernelGGL((split_gemm_kernel<MODE>), dim3(a.n_items), dim3(GM_THREADS), 0, s, a);
+  if (a.n_split > 0) {
+    hipLaunchKernelGGL(split_fixup_kernel, dim3(a.n_split * (GM_BM * GM_BN / 4 / 256)),
+                       dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 

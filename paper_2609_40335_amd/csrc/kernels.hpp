@@ -134,7 +134,7 @@ struct GemmArgs {
   float sigma_c, inv_b;
   uint32_t step;
   uint64_t seed;
-  // Tail split of the clipped sum (direct-load kernel): tiles [0, n_full) are
+  // Tail split of the clipped sum: tiles [0, n_full) are
   // whole work items; each of the n_split tiles after them is ksplit items
   // over consecutive K ranges, whose fp32 partial tiles (256 x 256, row-major)
   // go to part and are added by the fixup kernel. n_full = n_items, ksplit = 1
@@ -179,17 +179,27 @@ inline int sum_form(bool vec, int T, int B) {
 inline int norm_form(bool vec, int T) {
   return !vec ? FORM_STAGED : T % DL_SUM_BK == 0 ? FORM_PLAIN : FORM_RAGGED;
 }
-// The launches whose operands may span 4 GiB or more, and whose tail may be
-// split.
+// The launches whose operands may span 4 GiB or more.
 inline bool dl_sum_applies(int dt, bool vec, int T, int B) {
   return dt == DT_BF16 && vec && T % DL_SUM_BK == 0 && B <= DL_SUM_MAXB;
+}
+
+constexpr int SP_BK = 16;          // K rows per stage of the fp32 kernel
+// K stages of a clipped sum's launch.
+inline int sum_stages(int dt, bool vec, int T, int B) {
+  const int64_t K = (int64_t)B * T;
+  if (dt != DT_BF16) return (int)((K + SP_BK - 1) / SP_BK);
+  if (sum_form(vec, T, B) == FORM_ROWS) return (int)((K + DL_SUM_BK - 1) / DL_SUM_BK);
+  return (int)((int64_t)B * ((T + DL_SUM_BK - 1) / DL_SUM_BK));
 }
 
 // The last round of a launch of n_tiles equal tiles on `cus` CUs holds
 // r = n_tiles mod cus of them (all of them if n_tiles < cus). When r is at most
 // half the CUs, each of those tiles is split into ks consecutive K ranges of at
 // least 4 stages (ks <= 8, r * ks <= cus), so the round takes about 1/ks of a
-// tile's time.
+// tile's time. All forms of the sum are split alike: one 768 -> 3072 layer at
+// B = 24, T = 128 is 36 tiles (norm and sum: 84 us whole, 62 us split); the fp32
+// sums of DistilGPT2 there, 1239 tiles in two launches, took 2551 and take 2383 us.
 struct TailSplit {
   uint32_t n_full, n_split;
   int32_t ks;
@@ -235,7 +245,7 @@ inline int norm_group(uint64_t n_tiles, int B, int spe, int cus) {
 
 // Clipped sum: out (+)= sum_i c_i X_i^T Y_i over all B*T rows (K = B*T).
 // With a.part set (and room for the split that tail_split gives on `cus` CUs),
-// the direct-load kernel splits its last round and a fixup kernel follows.
+// the last round is split and a fixup kernel follows.
 hipError_t launch_clipped_sum(const GemmArgs& a, int dt, bool vec, int cus, size_t part_bytes,
                               hipStream_t s);
 // Direct norm: ws[b, slot] = ||tile of X_b^T Y_b||_F^2 for every output tile.

@@ -90,6 +90,8 @@ _SIGS = {
                              _VP, _SZ, _VP], _I),
     "dp_clipped_grad_sum_grouped": ([ctypes.POINTER(dp_linear_t), ctypes.POINTER(_VP), _I, _VP,
                                      _I, _I, _I, _I, _I, _VP], _I),
+    "dp_clipped_grad_sum_grouped_ws": ([ctypes.POINTER(dp_linear_t), ctypes.POINTER(_VP), _I, _VP,
+                                        _I, _I, _I, _I, _I, _VP, _SZ, _VP], _I),
     "dp_clipped_grad_sum_noised_grouped": ([ctypes.POINTER(dp_linear_t), ctypes.POINTER(_VP),
                                             ctypes.POINTER(_U64), ctypes.POINTER(ctypes.c_int32),
                                             _I, _VP, _I, _I, _I, _I, _F, _F, _I, _U64, _U64, _VP],
@@ -97,6 +99,8 @@ _SIGS = {
     "dp_add_noise": ([_VP, _I64, _F, _F, _I, _U64, _U64, _U64, _VP], _I),
     "dp_clipped_grad_sum_noised_grouped_workspace": ([ctypes.POINTER(dp_linear_t), _I, _I, _I, _I,
                                                       _I], _SZ),
+    "dp_clipped_grad_sum_split_workspace": ([ctypes.POINTER(dp_linear_t), _I, _I, _I, _I, _I],
+                                            _SZ),
     "dp_clipped_grad_sum_noised_grouped_ws": ([ctypes.POINTER(dp_linear_t), ctypes.POINTER(_VP),
                                                ctypes.POINTER(_U64), ctypes.POINTER(ctypes.c_int32),
                                                _I, _VP, _I, _I, _I, _I, _F, _F, _I, _U64, _U64,
@@ -178,6 +182,19 @@ def _stream(stream) -> int:
 
 def _ws(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
+
+
+def _split_ws(descs, n: int, B: int, T: int, dt: int, transpose_out, device, stream):
+    """Workspace of a clipped sum's split tail for a call on ``stream``, or None.
+    The stream is recorded: the memory may be reused once the call's kernels end."""
+    nbytes = lib().dp_clipped_grad_sum_split_workspace(descs, n, B, T, dt, int(transpose_out))
+    if not nbytes:
+        return None
+    ws = _ws(nbytes, device)
+    if stream is not None:
+        ws.record_stream(stream if isinstance(stream, torch.cuda.Stream)
+                         else torch.cuda.ExternalStream(stream.cuda_stream))
+    return ws
 
 
 def dp_abi_version() -> int:
@@ -340,9 +357,13 @@ def dp_clipped_grad_sum(A, G, c, out, ids=None, V: Optional[int] = None,
     if ids is None:
         _dev(A, "A")
         pa, _, _, d_in, lda = _rows(A, "A")
+        desc = (dp_linear_t * 1)(dp_linear_t(pa, lda, d_in, pg, ldg, d_out, DP_NORM_AUTO))
+        ws = _split_ws(desc, 1, B, T, dt, transpose_out, G.device, stream)
         _check(L.dp_clipped_grad_sum(pa, lda, pg, ldg, None, c.data_ptr(), B, T, d_in, d_out, dt,
-                                     int(transpose_out), out.data_ptr(), int(accumulate), None,
-                                     0, _stream(stream)), "dp_clipped_grad_sum")
+                                     int(transpose_out), out.data_ptr(), int(accumulate),
+                                     None if ws is None else ws.data_ptr(),
+                                     0 if ws is None else ws.numel(), _stream(stream)),
+               "dp_clipped_grad_sum")
         return out
     if A is not None or V is None:
         raise DPError("embedding form takes ids and V, not A")
@@ -728,6 +749,7 @@ class LinearGroup:
         nbytes = L.dp_ghost_norm_linear_bias_workspace(self.descs, self._bias, self.n, self.B,
                                                        self.T, self.dt)
         self.ws = _ws(nbytes, A0.device)
+        self._sum_ws_of = {}
         self.outs = None
         if outs is not None:
             self.set_outputs(outs)
@@ -750,10 +772,25 @@ class LinearGroup:
                     accumulate: bool = False, stream=None) -> None:
         if self.outs is None:
             raise DPError("set_outputs() first")
-        _check(lib().dp_clipped_grad_sum_grouped(self.descs, self.outs, self.n, c.data_ptr(),
-                                                 self.B, self.T, self.dt, int(transpose_out),
-                                                 int(accumulate), _stream(stream)),
-               "dp_clipped_grad_sum_grouped")
+        ws = self._sum_ws(transpose_out, stream)
+        _check(lib().dp_clipped_grad_sum_grouped_ws(self.descs, self.outs, self.n, c.data_ptr(),
+                                                    self.B, self.T, self.dt, int(transpose_out),
+                                                    int(accumulate),
+                                                    None if ws is None else ws.data_ptr(),
+                                                    0 if ws is None else ws.numel(),
+                                                    _stream(stream)),
+               "dp_clipped_grad_sum_grouped_ws")
+
+    def _sum_ws(self, transpose_out: bool, stream):
+        """The split tail's workspace, one per stream (sums on different streams
+        may overlap) and output layout, kept with the group."""
+        key = (bool(transpose_out), _stream(stream))
+        if key not in self._sum_ws_of:
+            self._sum_ws_of[key] = _split_ws(self.descs, self.n, self.B, self.T, self.dt,
+                                             transpose_out, self.ws.device,
+                                             torch.cuda.current_stream() if stream is None else stream)
+        self._split_ws = self._sum_ws_of[key]
+        return self._split_ws
 
     def clipped_sum_noised(self, c: torch.Tensor, tensor_ids: Sequence[int], sigma: float,
                            C: float, B_norm: int, seed: int, step: int, accumulate=None,
@@ -770,13 +807,7 @@ class LinearGroup:
             self._noise_arr = _noise_arrays(self.n, tensor_ids, accumulate)
         tids, acc = self._noise_arr
         L = lib()
-        if getattr(self, "_split_ws_key", None) != bool(transpose_out):
-            self._split_ws_key = bool(transpose_out)
-            nbytes = L.dp_clipped_grad_sum_noised_grouped_workspace(self.descs, self.n, self.B,
-                                                                    self.T, self.dt,
-                                                                    int(transpose_out))
-            self._split_ws = _ws(nbytes, self.ws.device) if nbytes else None
-        ws = self._split_ws
+        ws = self._sum_ws(transpose_out, stream)
         _check(L.dp_clipped_grad_sum_noised_grouped_ws(self.descs, self.outs, tids, acc, self.n,
                                                        c.data_ptr(), self.B, self.T, self.dt,
                                                        int(transpose_out), float(sigma), float(C),

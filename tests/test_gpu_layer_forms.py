@@ -121,7 +121,7 @@ def test_fp32_products_keep_their_bits(span):
         x = torch.randn(1, 1, w, generator=g, device="cuda")
         return x * torch.exp2(torch.randint(-span, span + 1, (1, 1, w), generator=g, device="cuda").float())
 
-    A, G = values(300), values(260)
+    A, G = values(300), values(260) * 2.0 ** -span   # (the norm must not overflow)
     out = torch.zeros(300, 260, device="cuda")
     dp.dp_clipped_grad_sum(A, G, torch.ones(1, device="cuda"), out)
     want = A.double().view(-1, 1) * G.double().view(1, -1)
@@ -130,3 +130,38 @@ def test_fp32_products_keep_their_bits(span):
         n2 = torch.zeros(1, device="cuda")
         dp.dp_ghost_norm_linear(A, G, n2, algo=algo)
         assert abs(float(n2) / float(want.square().sum()) - 1) <= 2.0 ** -19
+
+
+# B, T, d_in, d_out: forms of the sum whose last round is split over K (a few tiles, long K;
+# T a multiple of a stage or not; ranges that start inside an example)
+SPLIT = [(6, 160, 300, 264), (5, 100, 264, 300), (150, 9, 64, 320), (3, 515, 512, 40)]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("rows", ["aligned", "odd"])
+@pytest.mark.parametrize("shape", SPLIT, ids=lambda s: "x".join(map(str, s)))
+def test_split_sums_of_every_form(shape, rows, dtype):
+    """LinearGroup and the single call split few tiles over K and add the parts (fp32: the
+    same sum in another order, so the bound of the unsplit sum)."""
+    from paper_2609_40335_amd import dpghost as dp
+    B, T, di, do = shape
+    up = (lambda w: (w + 7) // 8 * 8) if rows == "aligned" else (lambda w: w + (1 - w % 2))
+    A, G, g = operands(3, B, T, di, do, dtype, up(di), up(do), 0 if rows == "aligned" else 3)
+    c = factors(B)
+    A[1] = float("inf")
+    Ac = torch.where(c.view(B, 1, 1) == 0, 0.0, A.double()) * c.double().view(B, 1, 1)
+    want = torch.einsum("km,kn->mn", Ac.reshape(B * T, di), G.double().reshape(B * T, do))
+    bound = 1e-5 if dtype == torch.float32 or 2 * (-T % 32) <= T else 5e-3
+    grp = dp.LinearGroup([(A, G)], [torch.full((di, do), float("nan"), device="cuda")])
+    grp.clipped_sum(c)
+    assert grp._split_ws is not None
+    assert float((grp._outs[0].double() - want).norm() / want.norm()) < bound
+    grp.clipped_sum_noised(c, [5], 0.5, 1.0, 3, 11, 2)
+    z = torch.zeros(di, do, device="cuda")
+    dp.dp_add_noise(z, 0.5, 1.0, 0, 11, 5, 2)
+    w = (want + z.double()) / 3
+    assert float((grp._outs[0].double() - w).norm() / w.norm()) < bound
+    out = torch.randn(do, di, generator=g, device="cuda")
+    w = want.t() + out.double()
+    dp.dp_clipped_grad_sum(A, G, c, out, transpose_out=True, accumulate=True)
+    assert float((out.double() - w).norm() / w.norm()) < bound
