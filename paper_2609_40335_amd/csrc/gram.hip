@@ -132,6 +132,22 @@ struct FpOff {  // a 64x64 quadrant of an off-diagonal pair; rows {x, x+32, y, y
   static constexpr int ia(int j) { return j >> 1; }
   static constexpr int ib(int j) { return 2 + (j & 1); }
 };
+template <int PAT>
+using PatFp = std::conditional_t<PAT == PAT_OFF, FpOff, std::conditional_t<PAT == PAT_D1, FpD1, FpD2>>;
+// The fragments' row offsets of wave w (those of block_rows).
+template <int PAT>
+__device__ __forceinline__ void pat_rows(int w, int (&rows)[PatFp<PAT>::NF]) {
+  int ra[4], rb[4];
+  float wt[4];
+  block_rows<PAT>(w, ra, rb, wt);
+  if constexpr (PAT == PAT_D1) {
+    rows[0] = ra[0]; rows[1] = ra[2];
+  } else if constexpr (PAT == PAT_D2) {
+    rows[0] = ra[0]; rows[1] = rb[0]; rows[2] = rb[1];
+  } else {
+    rows[0] = ra[0]; rows[1] = ra[2]; rows[2] = rb[0]; rows[3] = rb[1];
+  }
+}
 // Whole-example Gram (8 waves, block rows 0..7): wave g < 4 takes (g,g)..(g,g+4)
 // (rows g..g+4); waves 4..7 the rest of row pairs {g, 7-g}.
 struct FpW0 {
@@ -207,6 +223,42 @@ __device__ __forceinline__ void stage_mfma_fp(const u32x4* __restrict__ lds,
   }
 }
 
+// One fp32 stage (32 features per row) cut into bf16 planes (split_f32): plane
+// p holds ROWS rows of 4 chunks of 8 features, chunk c of row r at
+// pl_chunk(r, c), so that 16 rows' reads of one chunk touch all banks. The
+// SPLIT_TERMS plane products stand for one fp32 product.
+__device__ __forceinline__ int pl_chunk(int r, int c) { return r * 4 + (c ^ ((r >> 2) & 3)); }
+template <class P, int ROWS>
+__device__ __forceinline__ void stage_mfma_split(const u32x4* __restrict__ lds,
+                                                 const int (&rows)[P::NF], f32x16 (&acc)[P::NB],
+                                                 int lane) {
+  const int r32 = lane & 31, half = lane >> 5;
+  // A stage's products are summed from zero, small ones first, and added to the
+  // accumulator by the VALU. (The matrix core cuts what it adds below a fixed
+  // distance from the largest term: all on the accumulator, the many small
+  // same-signed terms of a squared norm lost 1.2e-6.)
+  auto frag = [&](int q, int ks, u32x4 (&f)[3]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      f[p] = lds[p * ROWS * 4 + pl_chunk(rows[q] + r32, 2 * ks + half)];
+  };
+  f32x16 sum[P::NB] = {};
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    u32x4 f[P::NF][3];
+#pragma unroll
+    for (int q = 0; q < P::NF; ++q) frag(q, ks, f[q]);
+#pragma unroll
+    for (int t = 0; t < SPLIT_TERMS; ++t)
+#pragma unroll
+      for (int j = 0; j < P::NB; ++j)
+        sum[j] = mfma32_bf16(f[P::ia(j)][split_a(t)], f[P::ib(j)][split_b(t)], sum[j]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int j = 0; j < P::NB; ++j) acc[j] += sum[j];
+}
+
 // Streams the rows of one or two T-tiles of a matrix pair through LDS.
 // Entry i (0..7) of a thread is LDS row (tid/8) + 32*i, chunk tid%8; entries
 // 0..3 are rows of T-tile ti, entries 4..7 rows of T-tile tj. Stage s < nX
@@ -266,15 +318,23 @@ struct TileStream {
     }
   }
 
-  // Writes a stage's entries to LDS.
-  template <int NENT>
+  // Writes a stage's entries to LDS (SPLIT: as three bf16 planes of 32 NENT rows).
+  template <int NENT, bool SPLIT>
   __device__ __forceinline__ void store(u32x4* lds, const u32x4 (&pre)[NENT], int tid) const {
 #pragma unroll
     for (int i = 0; i < NENT; ++i) {
       const int r = (tid >> 3) + 32 * i, cc = tid & 7;
       u32x4 v = pre[i];
       if (!VEC && (i < 4 ? ri : rj) + 32 * (i & 3) >= T) v = u32x4{0u, 0u, 0u, 0u};
-      lds[r * 8 + swz(r, cc)] = v;
+      if constexpr (!SPLIT) {
+        lds[r * 8 + swz(r, cc)] = v;
+      } else {
+        const Split2 x = split_f32(__uint_as_float(v[0]), __uint_as_float(v[1]));
+        const Split2 y = split_f32(__uint_as_float(v[2]), __uint_as_float(v[3]));
+        u32x2* const at = (u32x2*)(lds + pl_chunk(r, cc >> 1)) + (cc & 1);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) at[p * NENT * 32 * 8] = u32x2{x.p[p], y.p[p]};
+      }
     }
   }
 };
@@ -291,12 +351,24 @@ __device__ __forceinline__ void store_stage(u32x4* lds, const u32x4 (&pre)[NENT]
 // LDS of one stage: a diagonal pair streams 128 rows, an off-diagonal 256.
 template <int PAT> struct PatRows { static constexpr int ROWS = PAT == PAT_OFF ? 2 * GR_TM : GR_TM; };
 
+// fp32 examples of one T-tile multiply on the bf16 matrix cores (split_f32): the
+// fp32 MFMAs bounded them (norms of DistilGPT2 at B = 24, T = 128, V = 50257
+// unpadded: 780 us, 496 with it; error against fp64 8.4e-8, 2.7e-8 with it). Pairs of
+// T-tiles keep the fp32 MFMAs: the 256-row stages' planes and the partial sums
+// spilled registers and were up to 15 % slower (B = 8, T = 300, V = 50257).
+template <int DT, int PF>
+constexpr bool gram_split() { return DT == DT_F32 && PF == 2; }
+// 16-byte chunks of one stage in LDS: 128 bytes per row, or three planes of 64.
+template <int DT, int PF, int ROWS>
+constexpr int stage_chunks() { return ROWS * (gram_split<DT, PF>() ? 12 : 8); }
+
 template <int DT, bool VEC, int PAT, int PF>
 __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int ti, int tj, int chunk,
                            u32x4* lds) {
   constexpr int NB = PatNB<PAT>::NB;
   constexpr int ROWS = PatRows<PAT>::ROWS;
   constexpr int NENT = ROWS / 32;  // 16-byte chunks per thread per stage
+  constexpr bool SPLIT = gram_split<DT, PF>();
   using TS = TileStream<DT, VEC>;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -327,6 +399,15 @@ __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int
   int ra[4], rb[4];
   float wt[4];
   block_rows<PAT>(w, ra, rb, wt);
+  using FP = PatFp<PAT>;
+  static_assert(FP::NB == NB, "block list");
+  int rows[FP::NF];
+  pat_rows<PAT>(w, rows);
+  auto multiply = [&](const u32x4* st, f32x16 (&acc)[NB]) __attribute__((always_inline)) {
+    if constexpr (DT == DT_BF16) stage_mfma_fp<FP>(st, rows, acc, lane);
+    else if constexpr (SPLIT) stage_mfma_split<FP, ROWS>(st, rows, acc, lane);
+    else stage_mfma<DT, NB>(st, ra, rb, acc, lane);
+  };
   f32x16 accP[NB], accQ[NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j)
@@ -335,7 +416,7 @@ __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int
 
   const int n = ts.nX + nY;
   u32x4* buf0 = lds;
-  u32x4* buf1 = lds + ROWS * 8;
+  u32x4* buf1 = lds + stage_chunks<DT, PF, ROWS>();
   if constexpr (PF == 2) {
     // Two register sets and two LDS buffers: the loads of stage s+2 are in
     // flight while stage s is multiplied and stage s+1 is stored. Even
@@ -346,36 +427,36 @@ __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int
     auto phase = [&](int s_begin, int s_end, f32x16 (&acc)[NB]) {
       for (int s = s_begin; s < s_end; s += 2) {
         if (s + 2 < n) ts.template prefetch<NENT>(s + 2, pA);
-        stage_mfma<DT, NB>(buf0, ra, rb, acc, lane);
-        if (s + 1 < n) ts.template store<NENT>(buf1, pB, tid);
+        multiply(buf0, acc);
+        if (s + 1 < n) ts.template store<NENT, SPLIT>(buf1, pB, tid);
         __syncthreads();
         if (s + 1 >= s_end) break;
         if (s + 3 < n) ts.template prefetch<NENT>(s + 3, pB);
-        stage_mfma<DT, NB>(buf1, ra, rb, acc, lane);
-        if (s + 2 < n) ts.template store<NENT>(buf0, pA, tid);
+        multiply(buf1, acc);
+        if (s + 2 < n) ts.template store<NENT, SPLIT>(buf0, pA, tid);
         __syncthreads();
       }
     };
     ts.template prefetch<NENT>(0, pA);
     if (n > 1) ts.template prefetch<NENT>(1, pB);
-    ts.template store<NENT>(buf0, pA, tid);
+    ts.template store<NENT, SPLIT>(buf0, pA, tid);
     __syncthreads();
     phase(0, ts.nX, accP);
     phase(ts.nX, n, accQ);
   } else {
-    // One register set, two LDS buffers: the loads of stage s+1 are in
-    // flight while stage s is multiplied.
+    // One register set: the loads of stage s+1 are in flight while stage s is
+    // multiplied.
     u32x4 pA[NENT];
     auto phase = [&](int s_begin, int s_end, f32x16 (&acc)[NB]) {
       for (int s = s_begin; s < s_end; ++s) {
         if (s + 1 < n) ts.template prefetch<NENT>(s + 1, pA);
-        stage_mfma<DT, NB>((s & 1) ? buf1 : buf0, ra, rb, acc, lane);
-        if (s + 1 < n) ts.template store<NENT>((s & 1) ? buf0 : buf1, pA, tid);
+        multiply((s & 1) ? buf1 : buf0, acc);
+        if (s + 1 < n) ts.template store<NENT, SPLIT>((s & 1) ? buf0 : buf1, pA, tid);
         __syncthreads();
       }
     };
     ts.template prefetch<NENT>(0, pA);
-    ts.template store<NENT>(buf0, pA, tid);
+    ts.template store<NENT, SPLIT>(buf0, pA, tid);
     __syncthreads();
     phase(0, ts.nX, accP);
     phase(ts.nX, n, accQ);
@@ -392,15 +473,15 @@ __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int
 }
 
 // SINGLE: every example fits one T-tile (T <= 128), so only the diagonal
-// patterns exist; fewer registers and a 2 x 16 KB LDS footprint let three
+// patterns exist; fewer registers and 2 x 16 KB of LDS (fp32: 2 x 24 KB) let two
 // workgroups share a CU.
 template <int DT, bool VEC, bool SINGLE>
-__global__ __launch_bounds__(GR_THREADS) void gram_norm_kernel(GramArgs args) {
+__global__ __launch_bounds__(GR_THREADS, 2) void gram_norm_kernel(GramArgs args) {
   // Index the layer table in place in the kernel-argument segment (the only
   // explicit argument sits at offset 0) instead of copying it to the stack.
   const GramArgs& a = *(const GramArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   (void)args;
-  __shared__ u32x4 lds[2 * (SINGLE ? GR_TM : GR_ROWS) * 8];
+  __shared__ u32x4 lds[2 * stage_chunks<DT, SINGLE ? 2 : 1, SINGLE ? GR_TM : GR_ROWS>()];
   __shared__ float red[GR_THREADS / WAVE];
   const uint32_t item = xcd_remap(blockIdx.x, gridDim.x);
   const GramItem gi = gram_item(a, item);
@@ -594,17 +675,10 @@ __device__ __forceinline__ float dg_item(const GramLayer& L, int b, int T, int t
   int ra[4], rb[4];
   float wt[4];
   block_rows<PAT>(w, ra, rb, wt);
-  using FP = std::conditional_t<PAT == PAT_OFF, FpOff,
-                                std::conditional_t<PAT == PAT_D1, FpD1, FpD2>>;
+  using FP = PatFp<PAT>;
   static_assert(FP::NB == NB, "block list");
   int rows[FP::NF];
-  if constexpr (PAT == PAT_D1) {
-    rows[0] = ra[0]; rows[1] = ra[2];
-  } else if constexpr (PAT == PAT_D2) {
-    rows[0] = ra[0]; rows[1] = rb[0]; rows[2] = rb[1];
-  } else {
-    rows[0] = ra[0]; rows[1] = ra[2]; rows[2] = rb[0]; rows[3] = rb[1];
-  }
+  pat_rows<PAT>(w, rows);
   f32x16 accP[NB], accQ[NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j)

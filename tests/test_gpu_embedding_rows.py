@@ -133,3 +133,23 @@ def test_rows_beside_a_writer_of_out(dp):
     dp.dp_clipped_grad_sum(None, dEd, cd, ref, ids=idsd, V=V, accumulate=True)
     torch.cuda.synchronize()
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("transpose", [False, True])
+@pytest.mark.parametrize("B,T,d", [(5, 700, 70), (1, 31, 64), (2, 33, 5)],
+                         ids=["run-of-more-than-64-blocks", "part-block", "block-and-one"])
+def test_embedding_sum_adds_onto_a_prior(dp, B, T, d, transpose):
+    """Runs that end inside a block, span blocks and span more than 64 of them
+    (2048 tokens of one id), with invalid ids, added onto a prior matrix."""
+    V = 90
+    ids, dE, c, bad = _case(15, "bf16", B, T, V, d, "uniform", bad_every=11)
+    if B * T > 2048:
+        ids[:4] = 37                    # one run of 2800 tokens
+        bad[:4] = False
+    prior = gen.draw(16, 1, (V, d), 1.0, "f32")
+    ref = _oracle(ids, dE, c, bad, V, "bf16") + prior
+    out = dev(np.ascontiguousarray(prior.T if transpose else prior))
+    dp.dp_clipped_grad_sum(None, dev(dE, "bf16"), dev(c), out, ids=dev(ids), V=V,
+                           transpose_out=transpose, accumulate=True)
+    got = host(out)
+    assert_close(got.T if transpose else got, ref, TOL["bf16"])
