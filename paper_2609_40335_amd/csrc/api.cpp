@@ -201,7 +201,8 @@ int pick_chunks(int64_t width, int ks, int64_t items_per_chunk, int64_t other, i
 // as long as its longest item. Narrower chunks shorten it and fill idle
 // compute units, and each one repeats the layer's A stages. The choice
 // minimises max(longest item, stages per workgroup slot), with GRAM_FILL
-// stages per item for filling the ring and reducing the partials. (d_in = 768,
+// stages per item for filling the ring and reducing the partials; nothing is gained
+// below the length of the other layers' items (other_len). (d_in = 768,
 // d_out = 3072, B = 24, T = 128: the norm took 34 us of 109 for norm and sum,
 // 12 of 87 with it.) A launch of a full round or more keeps its items: each
 // chunk's repeated A stages then cost more than the shorter tail gains.
@@ -209,14 +210,15 @@ constexpr int GRAM_FILL = 6;
 struct GramShape {
   int64_t items, nx, ny;  // items per chunk; stages of A, of G
 };
-int few_items_chunk(const std::vector<GramShape>& v, int64_t other, int64_t slots) {
+int few_items_chunk(const std::vector<GramShape>& v, int64_t other, int64_t other_len,
+                    int64_t slots) {
   int64_t items = other;
   for (const GramShape& g : v) items += g.items;
   if (v.empty() || items >= slots) return 0;
   int best = 0;
   double best_cost = 0;
   for (int q : {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
-    int64_t longest = 0, total = 0;
+    int64_t longest = other_len, total = 0;
     for (const GramShape& g : v) {
       const int64_t len = g.nx + std::min<int64_t>(q, g.ny) + GRAM_FILL;
       longest = std::max(longest, len);
@@ -228,8 +230,9 @@ int few_items_chunk(const std::vector<GramShape>& v, int64_t other, int64_t slot
   return best;
 }
 
+// lean: no narrower chunks for few items (fewer partials).
 NormPlan plan_norm(const dp_linear_t* layers, int n, int B, int T, dp_dtype_t dt,
-                   float* const* bias = nullptr) {
+                   float* const* bias = nullptr, bool lean = false) {
   NormPlan p;
   p.n_t = (int)ceil_div(T, dpg::GR_TM);
   p.P = p.n_t * (p.n_t + 1) / 2;
@@ -257,7 +260,7 @@ NormPlan plan_norm(const dp_linear_t* layers, int n, int B, int T, dp_dtype_t dt
     plain_items[vec] += items;
   }
   std::vector<int> width(n, 0);       // features per chunk of the layers longer than KG_SPLIT
-  int64_t wide_items[2] = {0, 0};
+  int64_t wide_items[2] = {0, 0}, wide_len[2] = {0, 0};  // items, stages of the longest
   for (int i = 0; i < n; ++i) {
     const dp_linear_t& L = layers[i];
     if (use_direct(L, T) || L.d_out <= KG_SPLIT) continue;
@@ -266,9 +269,11 @@ NormPlan plan_norm(const dp_linear_t* layers, int n, int B, int T, dp_dtype_t dt
     const int nc = pick_chunks(L.d_out, ks, per_chunk, plain_items[vec] + wide_items[vec], slots);
     width[i] = (int)(ceil_div(ceil_div(L.d_out, nc), ks) * ks);
     wide_items[vec] += per_chunk * ceil_div(L.d_out, width[i]);
+    wide_len[vec] = std::max(wide_len[vec], ceil_div(L.d_in, ks) + width[i] / ks + GRAM_FILL);
   }
   int few[2];  // stages per G chunk where a launch is short of items, else 0
-  for (int v = 0; v < 2; ++v) few[v] = few_items_chunk(shapes[v], wide_items[v], slots);
+  for (int v = 0; v < 2; ++v)
+    few[v] = lean ? 0 : few_items_chunk(shapes[v], wide_items[v], wide_len[v], slots);
   for (int i = 0; i < n; ++i) {
     const dp_linear_t& L = layers[i];
     float* const bg = bias ? bias[i] : nullptr;
@@ -676,17 +681,27 @@ dp_status_t norm_bias_grouped(const dp_linear_t* layers, float* const* bias_grad
   dp_status_t st = check_layers(layers, n_layers, B, T, dt);
   if (st != DP_OK) return st;
   if (!norm2) return fail(DP_EINVAL, "norm2 is NULL");
-  const NormPlan p = plan_norm(layers, n_layers, B, T, dt, bias_grads);
+  // Where the plan's partials do not fit the static scratch (or their 31-bit index), the
+  // plan with fewer of them is used.
+  NormPlan p;
+  VecPlan vp;
+  size_t norm_bytes = 0, need = 0;
+  for (const bool lean : {false, true}) {
+    p = plan_norm(layers, n_layers, B, T, dt, bias_grads, lean);
+    vp = VecPlan{};
+    for (const BiasEntry& e : p.bias_vec)
+      plan_vec(vp, nullptr, 0, e.G, e.ldg, e.d, dpg::VEC_GRAD, e.grad, dt, T);
+    norm_bytes = norm_ws_bytes(p, B);
+    need = norm_bytes + align_up((size_t)B * vp.slots * 4);
+    if ((uint64_t)B * p.slots <= 0x7FFFFFFFull &&
+        !(use_static && need > (size_t)DP_NOALLOC_SCRATCH_BYTES))
+      break;
+  }
   if ((uint64_t)B * p.slots > 0x7FFFFFFFull) return fail(DP_EUNSUPPORTED, "too many partials");
   for (const BiasEntry& e : p.bias_vec)  // the vector kernel's offsets span the batch in 32 bits
     if (!span_ok((int64_t)B * T, e.ldg, dt))
       return fail(DP_EUNSUPPORTED, "a bias whose G spans 4 GiB or more must be fused into the "
                   "Gram launch (bf16, 16-byte rows, T <= 256)");
-  VecPlan vp;
-  for (const BiasEntry& e : p.bias_vec)
-    plan_vec(vp, nullptr, 0, e.G, e.ldg, e.d, dpg::VEC_GRAD, e.grad, dt, T);
-  const size_t norm_bytes = norm_ws_bytes(p, B);
-  const size_t need = norm_bytes + align_up((size_t)B * vp.slots * 4);
   if (use_static) {
     if (need > (size_t)DP_NOALLOC_SCRATCH_BYTES)
       return fail(DP_EUNSUPPORTED,

@@ -470,3 +470,21 @@ def test_split_tail_workspace(L):
     assert L.dp_clipped_grad_sum_noised_grouped_workspace(arr, 49, 32, 100, D.DP_BF16, 0) == 0
     # K = 64 rows = 2 stages: too short to split
     assert L.dp_clipped_grad_sum_noised_grouped_workspace(arr, 1, 2, 32, D.DP_BF16, 0) == 0
+
+
+
+def test_noalloc_plan_falls_back_to_fewer_partials(L):
+    """A launch of few items takes narrower G chunks, each with a partial: one example of
+    500 layers of 16776960 -> 32 features has more of them than the 8 MiB scratch holds. The call
+    keeps whole chunks then and goes on to the device (none here: DP_EHIP, not
+    DP_EUNSUPPORTED)."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch on pointers that hold nothing")
+    d = 65535 * 256
+    wide = D.dp_linear_t(1 << 40, d, d, 1 << 41, 32, 32, D.DP_NORM_GRAM)
+    arr = (D.dp_linear_t * 500)(*[wide] * 500)
+    assert L.dp_ghost_norm_linear_workspace(arr, 500, 1, 4, D.DP_F32) > 8 << 20
+    st = L.dp_ghost_norm_linear_bias_grouped_noalloc(arr, None, 500, 1, 4, D.DP_F32, 1 << 40, 0,
+                                                     None)
+    assert L.dp_status_string(st) == b"HIP error", L.dp_last_error()
