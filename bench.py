@@ -47,7 +47,7 @@ PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X dense fp32 matrix
 # HBM bytes per launch of the clipped-sum kernel: rocprofv3 FETCH_SIZE x 2 +
 # WRITE_SIZE x 1 (factors from a plain 1 GiB copy), recorded for the kernel
 # source with this SHA-256; any other source reports null.
-GEMM_TRAFFIC = {"gemm.hip sha256": "0e2bc51ebec82c8764d5ed3431f79329d1d6d9173b16c01b3326a7509a2ca79c",
+GEMM_TRAFFIC = {"gemm.hip sha256": "860886f34ee4ab704e76273f9181c1c00763de78e3d50e729ec42bb66e3afcfc",
                 "bytes": 2697737984}
 
 

@@ -555,9 +555,9 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
 }
 
 // ---------------------------------------------------------------------------
-// Direct-load kernel for the bf16 clipped sum and direct norm (16-byte
-// aligned rows, T a multiple of 32; B <= 4096 for the clipped sum's factor
-// table): no staging through VGPRs at all.
+// Direct-load kernel for the bf16 clipped sum and direct norm. In its PLAIN, BIG
+// and RAGGED forms (16-byte aligned rows; see GemmForm) nothing is staged
+// through VGPRs; the STAGED and ROWS forms load through registers further down.
 //
 // Global rows go straight into LDS through buffer loads that write LDS
 // (each lane's 16 bytes land at M0 + 16*lane), so LDS keeps the token-major
@@ -592,8 +592,10 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
 // bookkeeping stays sound: untracked loads only make its own waits stricter.
 // Clip factors are staged in LDS so that the loop issues no other vector
 // memory instruction; each is read one example ahead, so that a rescale never
-// waits behind the fragment reads. Scaling is on the fp32 accumulators as in
-// SC_ACC. In the direct norm the example boundary instead squares and sums
+// waits behind the fragment reads. Scaling is on the fp32 accumulators:
+// rescaled by c_prev / c_next at example boundaries and by the last factor at the
+// end, examples with c = 0 skipped (so that inf or NaN in their rows adds
+// nothing). In the direct norm the example boundary instead squares and sums
 // each wave's part of the tile (and writes the tile to the gradient store,
 // if there is one), then clears the accumulators for the next example.
 constexpr int DL_BK = DL_SUM_BK;            // k rows per stage
