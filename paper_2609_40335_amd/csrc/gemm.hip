@@ -1112,6 +1112,7 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
     };
     Set q;
     load_set(0, q);
+    if constexpr (ROWS) bar();  // write_set reads the factor table, which every wave fills
     write_set(0, q);
     load_set(1, q);
     write_set(1, q);

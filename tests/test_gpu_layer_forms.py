@@ -165,3 +165,33 @@ def test_split_sums_of_every_form(shape, rows, dtype):
     w = want.t() + out.double()
     dp.dp_clipped_grad_sum(A, G, c, out, transpose_out=True, accumulate=True)
     assert float((out.double() - w).norm() / w.norm()) < bound
+
+
+@pytest.mark.parametrize("B,T,di,do", [(600, 7, 40, 72), (40, 21, 264, 64), (64, 40, 64, 300)],
+                         ids=lambda s: str(s))
+def test_each_call_scales_by_its_own_factors(B, T, di, do):
+    """Short bf16 sequences, whose rows are scaled from the factor table while they are
+    staged: calls queued back to back, each with other factors, so that factors of an earlier
+    call (or a table that is not yet filled) would show. One example of the first 64 rows is
+    left out and holds inf. B = 600 takes two rounds of 512 threads to fill the table."""
+    from paper_2609_40335_amd import dpghost as dp
+    A, G, g = operands(4, B, T, di, do, torch.bfloat16, di, do, 0)
+    cs, outs = [], []
+    for i in range(12):
+        c = torch.rand(B, device="cuda", generator=g) * 0.9 + 0.1
+        c[i % 3] = 0.0
+        cs.append(c)
+        outs.append(torch.full((di, do), float("nan"), device="cuda"))
+    inputs = []
+    for i in range(3):
+        Ai = A.clone()
+        Ai[i] = float("inf")
+        inputs.append(Ai)
+    for i in range(12):
+        dp.dp_clipped_grad_sum(inputs[i % 3], G, cs[i], outs[i])
+    for i in range(12):
+        c = cs[i].double().view(B, 1, 1)
+        Ac = torch.where(c == 0, 0.0, A.double()) * c
+        want = Ac.reshape(B * T, di).t() @ G.double().reshape(B * T, do)
+        rel = float((outs[i].double() - want).norm() / want.norm())
+        assert rel < 5e-3, (i, rel)
