@@ -9,6 +9,7 @@ fallback: if the library is not built, loading it raises.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from typing import Optional, Sequence
@@ -180,21 +181,26 @@ def _stream(stream) -> int:
     return s.cuda_stream
 
 
-def _ws(nbytes: int, device) -> torch.Tensor:
-    return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
+def _on(stream):
+    """Context whose allocations come from ``stream``'s own pool. A call's scratch must:
+    the current stream's pool hands out memory that kernels queued there may still use,
+    which only calls on that same stream wait for."""
+    if stream is None:
+        return contextlib.nullcontext()
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
+    return torch.cuda.stream(stream)
 
 
-def _split_ws(descs, n: int, B: int, T: int, dt: int, transpose_out, device, stream):
-    """Workspace of a clipped sum's split tail for a call on ``stream``, or None.
-    The stream is recorded: the memory may be reused once the call's kernels end."""
-    nbytes = lib().dp_clipped_grad_sum_split_workspace(descs, n, B, T, dt, int(transpose_out))
-    if not nbytes:
-        return None
-    ws = _ws(nbytes, device)
-    if stream is not None:
-        ws.record_stream(stream if isinstance(stream, torch.cuda.Stream)
-                         else torch.cuda.ExternalStream(stream.cuda_stream))
-    return ws
+def _ws(nbytes: int, device, stream=None) -> torch.Tensor:
+    """Scratch of a call on ``stream`` (None: the current one)."""
+    with _on(stream):
+        return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
+
+
+def _split_bytes(descs, n: int, B: int, T: int, dt: int, transpose_out) -> int:
+    """Workspace bytes of a clipped sum's split tail (0: nothing is split)."""
+    return lib().dp_clipped_grad_sum_split_workspace(descs, n, B, T, dt, int(transpose_out))
 
 
 def dp_abi_version() -> int:
@@ -216,7 +222,9 @@ def dp_ghost_norm_linear_bias_grouped(layers: Sequence, bias_grads: Sequence, no
                                       accumulate: bool = False, stream=None) -> torch.Tensor:
     """The grouped norm that also writes bias_grads[l] (fp32 [B, d_out], or
     None for a layer without bias) = sum over tokens of G_l, norms included."""
-    return LinearGroup(layers, bias_grads=bias_grads).ghost_norm(norm2, accumulate, stream)
+    with _on(stream):  # the group and its workspace live for this call only
+        group = LinearGroup(layers, bias_grads=bias_grads)
+    return group.ghost_norm(norm2, accumulate, stream)
 
 
 def dp_ghost_norm_linear_bias_grouped_noalloc(layers: Sequence, bias_grads: Optional[Sequence],
@@ -261,7 +269,7 @@ def dp_ghost_norm_linear_grouped(layers: Sequence, norm2: torch.Tensor, accumula
     arr = (dp_linear_t * len(descs))(*descs)
     dt = _dtype(A0)
     nbytes = L.dp_ghost_norm_linear_workspace(arr, len(descs), B, T, dt)
-    ws = _ws(nbytes, A0.device)
+    ws = _ws(nbytes, A0.device, stream)
     _check(L.dp_ghost_norm_linear_grouped(arr, len(descs), B, T, dt, norm2.data_ptr(),
                                           int(accumulate), ws.data_ptr(), ws.numel(),
                                           _stream(stream)), "dp_ghost_norm_linear_grouped")
@@ -275,7 +283,7 @@ def dp_ghost_norm_linear(A, G, norm2, accumulate: bool = False, algo: int = DP_N
     B, T = A.shape[0], A.shape[1]
     dt = _dtype(A)
     nbytes = L.dp_ghost_norm_linear_workspace(ctypes.byref(d), 1, B, T, dt)
-    ws = _ws(nbytes, A.device)
+    ws = _ws(nbytes, A.device, stream)
     _check(L.dp_ghost_norm_linear(d.A, d.lda, d.G, d.ldg, B, T, d.d_in, d.d_out, dt, algo,
                                   norm2.data_ptr(), int(accumulate), ws.data_ptr(), ws.numel(),
                                   _stream(stream)), "dp_ghost_norm_linear")
@@ -289,7 +297,7 @@ def dp_ghost_norm_embedding(ids, dE, V: int, norm2, accumulate: bool = False, se
     pe, B, T, d, lde = _rows(dE, "dE")
     if ids.dtype != torch.int32 or tuple(ids.shape) != (B, T) or not ids.is_contiguous():
         raise DPError("ids must be contiguous int32 [B, T]")
-    ws = _ws(L.dp_ghost_norm_embedding_workspace(B, T, d), dE.device)
+    ws = _ws(L.dp_ghost_norm_embedding_workspace(B, T, d), dE.device, stream)
     _check(L.dp_ghost_norm_embedding(ids.data_ptr(), pe, lde, B, T, V, d, _dtype(dE),
                                      norm2.data_ptr(), int(accumulate),
                                      None if seg_id is None else seg_id.data_ptr(),
@@ -312,7 +320,7 @@ def dp_tied_cross_term(ids, dE, H, Gz, V: int, out, scale: float = 1.0,
         raise DPError("Gz must have at least V columns")
     if ids.dtype != torch.int32 or tuple(ids.shape) != (B, T) or not ids.is_contiguous():
         raise DPError("ids must be contiguous int32 [B, T]")
-    ws = _ws(L.dp_tied_cross_term_workspace(B, T, d), dE.device)
+    ws = _ws(L.dp_tied_cross_term_workspace(B, T, d), dE.device, stream)
     _check(L.dp_tied_cross_term(ids.data_ptr(), pe, lde, ph, ldh, pz, ldz, B, T, V, d,
                                 _dtype(dE), float(scale), out.data_ptr(), int(accumulate),
                                 ws.data_ptr(), ws.numel(), _stream(stream)),
@@ -358,7 +366,8 @@ def dp_clipped_grad_sum(A, G, c, out, ids=None, V: Optional[int] = None,
         _dev(A, "A")
         pa, _, _, d_in, lda = _rows(A, "A")
         desc = (dp_linear_t * 1)(dp_linear_t(pa, lda, d_in, pg, ldg, d_out, DP_NORM_AUTO))
-        ws = _split_ws(desc, 1, B, T, dt, transpose_out, G.device, stream)
+        nbytes = _split_bytes(desc, 1, B, T, dt, transpose_out)
+        ws = _ws(nbytes, G.device, stream) if nbytes else None
         _check(L.dp_clipped_grad_sum(pa, lda, pg, ldg, None, c.data_ptr(), B, T, d_in, d_out, dt,
                                      int(transpose_out), out.data_ptr(), int(accumulate),
                                      None if ws is None else ws.data_ptr(),
@@ -369,7 +378,7 @@ def dp_clipped_grad_sum(A, G, c, out, ids=None, V: Optional[int] = None,
         raise DPError("embedding form takes ids and V, not A")
     if ids.dtype != torch.int32 or tuple(ids.shape) != (B, T) or not ids.is_contiguous():
         raise DPError("ids must be contiguous int32 [B, T]")
-    ws = _ws(L.dp_clipped_grad_sum_workspace(B, T, d_out, 1), G.device)
+    ws = _ws(L.dp_clipped_grad_sum_workspace(B, T, d_out, 1), G.device, stream)
     _check(L.dp_clipped_grad_sum(None, 0, pg, ldg, ids.data_ptr(), c.data_ptr(), B, T, V, d_out,
                                  dt, int(transpose_out), out.data_ptr(), int(accumulate),
                                  ws.data_ptr(), ws.numel(), _stream(stream)),
@@ -522,7 +531,7 @@ def dp_vector_grads_grouped(params: Sequence, grads: Sequence[torch.Tensor], nor
     if len(grads) != len(params):
         raise DPError("one gradient buffer per parameter")
     gp = (ctypes.c_void_p * len(grads))(*[g.data_ptr() for g in grads])
-    ws = _ws(L.dp_vector_grads_workspace(descs, len(params), B, T, dt), G0.device)
+    ws = _ws(L.dp_vector_grads_workspace(descs, len(params), B, T, dt), G0.device, stream)
     _check(L.dp_vector_grads_grouped(descs, len(params), B, T, dt, gp,
                                      None if norm2 is None else norm2.data_ptr(), int(accumulate),
                                      ws.data_ptr(), ws.numel(), _stream(stream)),
@@ -589,7 +598,7 @@ def dp_ghost_norm_positional(dE, norm2, accumulate: bool = False, stream=None) -
     L = lib()
     _dev(dE, "dE")
     pe, B, T, d, lde = _rows(dE, "dE")
-    ws = _ws(L.dp_ghost_norm_positional_workspace(B, T, d), dE.device)
+    ws = _ws(L.dp_ghost_norm_positional_workspace(B, T, d), dE.device, stream)
     _check(L.dp_ghost_norm_positional(pe, lde, B, T, d, _dtype(dE), norm2.data_ptr(),
                                       int(accumulate), ws.data_ptr(), ws.numel(), _stream(stream)),
            "dp_ghost_norm_positional")
@@ -749,7 +758,7 @@ class LinearGroup:
         nbytes = L.dp_ghost_norm_linear_bias_workspace(self.descs, self._bias, self.n, self.B,
                                                        self.T, self.dt)
         self.ws = _ws(nbytes, A0.device)
-        self._sum_ws_of = {}
+        self._sum_bytes = {}
         self.outs = None
         if outs is not None:
             self.set_outputs(outs)
@@ -782,15 +791,16 @@ class LinearGroup:
                "dp_clipped_grad_sum_grouped_ws")
 
     def _sum_ws(self, transpose_out: bool, stream):
-        """The split tail's workspace, one per stream (sums on different streams
-        may overlap) and output layout, kept with the group."""
-        key = (bool(transpose_out), _stream(stream))
-        if key not in self._sum_ws_of:
-            self._sum_ws_of[key] = _split_ws(self.descs, self.n, self.B, self.T, self.dt,
-                                             transpose_out, self.ws.device,
-                                             torch.cuda.current_stream() if stream is None else stream)
-        self._split_ws = self._sum_ws_of[key]
-        return self._split_ws
+        """The split tail's workspace: every call's own, as calls on other streams
+        and replays of a captured one may overlap. Its size is kept per layout."""
+        key = bool(transpose_out)
+        if key not in self._sum_bytes:
+            self._sum_bytes[key] = _split_bytes(self.descs, self.n, self.B, self.T, self.dt, key)
+        self._split_ws = None
+        nbytes = self._sum_bytes[key]
+        ws = _ws(nbytes, self.ws.device, stream) if nbytes else None
+        self._split_ws = ws
+        return ws
 
     def clipped_sum_noised(self, c: torch.Tensor, tensor_ids: Sequence[int], sigma: float,
                            C: float, B_norm: int, seed: int, step: int, accumulate=None,

@@ -195,3 +195,48 @@ def test_each_call_scales_by_its_own_factors(B, T, di, do):
         want = Ac.reshape(B * T, di).t() @ G.double().reshape(B * T, do)
         rel = float((outs[i].double() - want).norm() / want.norm())
         assert rel < 5e-3, (i, rel)
+
+
+def test_split_sums_on_two_streams_and_in_a_graph():
+    """Split sums queued on the current stream and, by `stream`, on another at the same time,
+    then a captured one replayed on the second stream beside eager calls on the first: every
+    call has partial tiles of its own, so each result keeps its bits."""
+    from paper_2609_40335_amd import dpghost as dp
+    B, T, di, do = 24, 128, 768, 768
+    sets = []
+    for seed in (5, 6):
+        A, G, _ = operands(seed, B, T, di, do, torch.bfloat16, di, do, 0)
+        sets.append((A, G, torch.linspace(0.05 * seed, 1.0, B, device="cuda")))
+    grps = [dp.LinearGroup([(A, G)], [torch.zeros(di, do, device="cuda")]) for A, G, _ in sets]
+    want = []
+    for (A, G, c), grp in zip(sets, grps):
+        grp.clipped_sum(c)
+        assert grp._split_ws is not None
+        want.append(grp._outs[0].clone())
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    outs = [[torch.zeros(di, do, device="cuda") for _ in range(8)] for _ in sets]
+    torch.cuda.synchronize()
+    for i in range(8):
+        for k, (A, G, c) in enumerate(sets):
+            dp.dp_clipped_grad_sum(A, G, c, outs[k][i], stream=side if k else None)
+    torch.cuda.synchronize()
+    for k in range(2):
+        for o in outs[k]:
+            assert torch.equal(o, want[k])
+    graph = torch.cuda.CUDAGraph()
+    grps[1].clipped_sum(sets[1][2], stream=side)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        grps[1].clipped_sum(sets[1][2], stream=side)
+    for i in range(4):
+        for grp in grps:
+            grp._outs[0].fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            graph.replay()
+        for _ in range(3):
+            grps[0].clipped_sum(sets[0][2])
+        torch.cuda.synchronize()
+        for grp, w in zip(grps, want):
+            assert torch.equal(grp._outs[0], w)
