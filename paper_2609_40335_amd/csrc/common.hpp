@@ -1,6 +1,7 @@
 // Shared device helpers for the gfx950 (CDNA4) kernels of libdpghost.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <stdint.h>
 
 #include "kernels.hpp"
@@ -107,14 +108,18 @@ __device__ __forceinline__ f32x16 mfma32_f32(float a, float b, const f32x16& c) 
 }
 
 // fp32 products on the bf16 matrix cores: a value is cut exactly into three bf16
-// planes, x = x0 + x1 + x2: x0 its upper 16 bits (cut off, so that nothing
-// overflows), x1 the rest rounded to nearest, x2 what is left (8 bits at most).
-// |x1| <= 2^-7 |x|, |x2| <= 2^-16 |x|, and the sign of x2 is that of a
-// rounding error. A product is the sum of the SPLIT_TERMS plane products
-// below, smallest first; the ones left out (x1 y2, x2 y1, x2 y2) are at most
-// 2^-22 and about 2^-26 of it on average, with signs as random as a rounding's.
-// Values below 2^-102 lose low bits in the planes (bf16 ends at 2^-126), and an
-// infinity's planes hold NaN (inf - inf), so that it gives NaN.
+// planes, x = x0 + x1 + x2, each what is left rounded to nearest (the last is
+// exact: 8 bits at most are left): |x1| <= 2^-8 |x|, |x2| <= 2^-17 |x|. A product
+// is the sum of the SPLIT_TERMS plane products below, smallest first; the ones
+// left out (x1 y2, x2 y1, x2 y2) are at most 2^-24 of it, the most that the
+// rounding of an fp32 product is off, and about 2^-27 as a root mean square.
+// (Published for reduced-precision matrix units as the BF16x3 / three-term split,
+// G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", 2019.)
+// Values below 2^-110 lose low bits in the planes (bf16 ends at 2^-133). Values
+// above bf16's largest and infinities make planes of infinities and NaN, and a product
+// that overflows may do so with both signs. Results that may come from such values
+// are computed again on the fp32 matrix cores.
 constexpr int SPLIT_TERMS = 6;
 __device__ __forceinline__ constexpr int split_a(int t) {
   return t == 0 ? 0 : t == 1 ? 2 : t == 2 ? 1 : t == 3 ? 0 : t == 4 ? 1 : 0;
@@ -127,15 +132,26 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // Two values' planes, two bf16 per dword.
 struct Split2 { uint32_t p[3]; };
 __device__ __forceinline__ Split2 split_f32(float a, float b) {
-  constexpr uint32_t HIGH = 0x07060302u;  // the upper halves of two dwords
-  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
   Split2 s;
-  s.p[0] = __builtin_amdgcn_perm(ub, ua, HIGH);
-  const float ra = a - __uint_as_float(ua & 0xFFFF0000u), rb = b - __uint_as_float(ub & 0xFFFF0000u);
+  s.p[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+  const float ra = a - __uint_as_float(s.p[0] << 16), rb = b - __uint_as_float(s.p[0] & 0xFFFF0000u);
   s.p[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
   const float la = ra - __uint_as_float(s.p[1] << 16), lb = rb - __uint_as_float(s.p[1] & 0xFFFF0000u);
-  s.p[2] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), HIGH);
+  s.p[2] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);  // upper halves
   return s;
+}
+
+// s + the five small products of 16 k of a block, smallest first.
+__device__ __forceinline__ f32x16 split_small(const u32x4 (&a)[3], const u32x4 (&b)[3], f32x16 s) {
+#pragma unroll
+  for (int t = 0; t < SPLIT_TERMS - 1; ++t) s = mfma32_bf16(a[split_a(t)], b[split_b(t)], s);
+  return s;
+}
+// Opaque, so that the additions stay where they are written instead of moving
+// behind all of a stage's products, whose sums would have to be kept.
+__device__ __forceinline__ void split_add(f32x16& to, const f32x16& from) {
+  to += from;
+  asm volatile("" : "+v"(to));
 }
 
 // Buffer resources: loads through them need no bounds branches, because the

@@ -317,14 +317,22 @@ __global__ __launch_bounds__(256) void split_fixup_kernel(GemmArgs args) {
 
 // The fp32 clipped sum and direct norm: split_gemm_kernel. Every fp32 operand
 // is cut exactly into three bf16 planes (split_f32 in common.hpp), and a
-// product becomes six bf16 ones, the planes' products down to 2^-18 of it;
-// the dropped ones are below 2^-25 of it, like the rounding of an fp32
-// product. Six 32x32x16 bf16 MFMAs take 192 cycles where the eight fp32
-// 32x32x2 ones for the same 16 k take 512. The clipped sums of DistilGPT2 at
-// B = 24, T = 128, V = 50257 unpadded (498 GFLOP): 5171 us on the fp32 MFMAs
-// (96 TFLOP/s of the 157 they peak at, 154 in a large library product), 2551
-// us here (195 TFLOP/s, 1.17 PFLOP/s in bf16 terms), with an error against
-// fp64 of 7.7e-7 where the fp32 MFMAs gave 9.3e-7.
+// product becomes six bf16 ones. Six 32x32x16 bf16 MFMAs take 192 cycles where
+// the eight fp32 32x32x2 ones for the same 16 k take 512. A block's products
+// of a stage are summed from zero, the large one (x0 y0) apart from the five
+// small ones, and the VALU adds both sums to the accumulator: the matrix core
+// cuts off, always towards zero, what lies below a fixed distance from the
+// largest term of a sum, and with all six products on the running accumulator
+// direct norms of operands of one sign were up to 6 times further from fp64
+// than with fp32 MFMAs (1.9e-7 for 4.3e-8 at T = 1024, GELU outputs and softmax
+// gradients; 4.1e-8 now). The clipped sums of DistilGPT2 at B = 24, T = 128,
+// V = 50257 unpadded (498 GFLOP): 5165 us on the fp32 MFMAs, 2307 us on the
+// running accumulator, 2950 us here, bound by the matrix core and the VALU
+// alike (256 additions and about 110 conversions per lane and stage beside 48
+// MFMAs). Their error against fp64 is a third of the fp32 MFMAs' (3.2e-7 to
+// 9.5e-7 of normal operands); it is larger only where the products of 16
+// tokens spread over many binary orders and K is short (lognormal operands of
+// sigma 2: norms 2.3e-7 for 1.4e-7 at T = 32, less than theirs from T = 200 on).
 //
 // Tile 256x256, 16 k per stage, 8 waves of 128x64 as in the bf16 kernel.
 // Waves 0-3 stage X, waves 4-7 Y: a wave takes 8 k rows and 128 columns, a
@@ -472,30 +480,32 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
   const u32x4* const rd_x = lds + half * GM_BM + wm * 64 + sp_slot(r32);
   const u32x4* const rd_y = lds + SP_OP + half * GM_BM + wn * 32 + sp_slot(r32);
   auto compute = [&](int buf) __attribute__((always_inline)) {
-    // The next block row's fragments are read while this one's are multiplied.
-    // Fences bound how far the reads move up (all at once, they spill).
+    // The sum of a block's large products is added to its accumulator while the
+    // next block is multiplied. Fences bound how far the reads move up (all at
+    // once, they spill).
     const u32x4* const bx = rd_x + buf * SP_STAGE;
     const u32x4* const by = rd_y + buf * SP_STAGE;
-    u32x4 y[2][3], x[2][3];
+    u32x4 y[2][3], x[3];
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-      x[0][p] = bx[p * SP_PLANE];
       y[0][p] = by[p * SP_PLANE];
       y[1][p] = by[p * SP_PLANE + 16];
     }
+    f32x16 big;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (i < 3) {
+    for (int q = 0; q < 8; ++q) {
+      const int i = q >> 1, j = q & 1;
+      if (j == 0) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p) x[(i + 1) & 1][p] = bx[p * SP_PLANE + (i + 1) * 16];
+        for (int p = 0; p < 3; ++p) x[p] = bx[p * SP_PLANE + i * 16];
       }
-#pragma unroll
-      for (int t = 0; t < SPLIT_TERMS; ++t)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = mfma32_bf16(x[i & 1][split_a(t)], y[j][split_b(t)], acc[i][j]);
+      const f32x16 small = split_small(x, y[j], f32x16{});
+      if (q > 0) split_add(acc[(q - 1) >> 1][(q - 1) & 1], big);
+      big = mfma32_bf16(x[0], y[j][0], f32x16{});
+      split_add(acc[i][j], small);
       __builtin_amdgcn_sched_barrier(0);
     }
+    split_add(acc[3][1], big);
   };
 
   load();
@@ -519,7 +529,68 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
     __syncthreads();
   }
 
+  // f(value) over this lane's elements inside the matrix.
+  auto each = [&](auto f) __attribute__((always_inline)) {
+    // Rows and columns left in the tile past this lane's first element. Opaque, so
+    // that the elements' masks are not kept from one use to the next.
+    int lim_m = (int)(L.M - m0) - (wm * 128 + (lane >> 5) * 4);
+    int lim_n = (int)(L.N - n0) - (wn * 64 + (lane & 31));
+    asm volatile("" : "+v"(lim_m), "+v"(lim_n));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bool nin = j * 32 < lim_n;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          f(nin && i * 32 + (e >> 2) * 8 + (e & 3) < lim_m ? acc[i][j][e] : 0.f);
+      }
+  };
+  // The wave's part of the tile on the fp32 matrix cores, from memory. An
+  // infinity's planes hold NaN, and where a product overflows, plane products
+  // of both signs may: a result that is not finite is computed again with this,
+  // so that it is the infinity or NaN that fp32 products give. So is a sum of values
+  // so small that their planes may have lost bits (all results below 2^-60).
+  auto again = [&]() __attribute__((always_inline)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));  // no address of this loop is kept across the main one
+    const int k_end = min((s0 + nS) * SP_BK, rows);
+    const int64_t row0 = MODE == MODE_NORM ? (int64_t)b * a.T : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
+#pragma unroll 1
+    for (int k0 = s0 * SP_BK; k0 < k_end; k0 += 2) {
+      const int k = k0 + (ln >> 5);
+      const bool kin = k < k_end;
+      const float c = MODE == MODE_SUM && kin ? a.c[k / nT] : 1.f;
+      const bool use = kin && c != 0.f;
+      float xf[4], yf[2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int64_t m = m0 + wm * 128 + i * 32 + (ln & 31);
+        xf[i] = use && m < L.M ? ((const float*)L.X)[(row0 + k) * L.ldx + m] * c : 0.f;
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int64_t n = n0 + wn * 64 + j * 32 + (ln & 31);
+        yf[j] = use && n < L.N ? ((const float*)L.Y)[(row0 + k) * L.ldy + n] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma32_f32(xf[i], yf[j], acc[i][j]);
+    }
+  };
+
   if constexpr (MODE == MODE_SUM) {
+    float z = 0.f, top = 0.f;  // z: NaN if any element is not finite
+    each([&](float v) {
+      z = fmaf(v, 0.f, z);
+      top = fmaxf(top, fabsf(v));
+    });
+    if (__any(z != z) || (!__any(top >= 0x1p-60f) && __any(top > 0.f))) again();
     float* const slice = (float*)lds + w * 32 * EP_LD;
     // The host orders every launch so that the kernel's rows are the output's.
     if (kc < 0)
@@ -528,20 +599,14 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
       store_partial(a.part + ((size_t)(item - a.n_full) * a.ksplit + kc) * (GM_BM * GM_BN), wm, wn,
                     lane, acc, slice);
   } else {
-    const int lim_m = (int)(L.M - m0) - (wm * 128 + (lane >> 5) * 4);
-    const int lim_n = (int)(L.N - n0) - (wn * 64 + (lane & 31));
     float part = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bool nin = j * 32 < lim_n;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float v = acc[i][j][e];
-          part += (nin && i * 32 + (e >> 2) * 8 + (e & 3) < lim_m) ? v * v : 0.f;
-        }
-      }
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+      part = 0.f;
+      each([&](float v) { part += v * v; });
+      if (pass == 1 || !__any(!(part <= FLT_MAX))) break;
+      again();
+    }
     part = wave_sum(part);
     if (lane == 0) red[w] = part;
     __syncthreads();

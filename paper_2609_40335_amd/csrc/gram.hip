@@ -226,37 +226,36 @@ __device__ __forceinline__ void stage_mfma_fp(const u32x4* __restrict__ lds,
 // One fp32 stage (32 features per row) cut into bf16 planes (split_f32): plane
 // p holds ROWS rows of 4 chunks of 8 features, chunk c of row r at
 // pl_chunk(r, c), so that 16 rows' reads of one chunk touch all banks. The
-// SPLIT_TERMS plane products stand for one fp32 product.
+// SPLIT_TERMS plane products stand for one fp32 product; a stage's large ones and
+// its small ones are summed from zero, apart, and added to the accumulator by
+// the VALU. (The matrix core cuts what it adds towards zero below a fixed distance from
+// the largest term: all on the accumulator, the many same-signed terms of a squared
+// norm lost 1.2e-6; both kinds in one sum, norms of softmax gradients 8e-8 at T = 128.)
 __device__ __forceinline__ int pl_chunk(int r, int c) { return r * 4 + (c ^ ((r >> 2) & 3)); }
 template <class P, int ROWS>
 __device__ __forceinline__ void stage_mfma_split(const u32x4* __restrict__ lds,
                                                  const int (&rows)[P::NF], f32x16 (&acc)[P::NB],
                                                  int lane) {
   const int r32 = lane & 31, half = lane >> 5;
-  // A stage's products are summed from zero, small ones first, and added to the
-  // accumulator by the VALU. (The matrix core cuts what it adds below a fixed
-  // distance from the largest term: all on the accumulator, the many small
-  // same-signed terms of a squared norm lost 1.2e-6.)
-  auto frag = [&](int q, int ks, u32x4 (&f)[3]) __attribute__((always_inline)) {
+  u32x4 f[2][P::NF][3];
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
-      f[p] = lds[p * ROWS * 4 + pl_chunk(rows[q] + r32, 2 * ks + half)];
-  };
-  f32x16 sum[P::NB] = {};
+  for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    u32x4 f[P::NF][3];
+    for (int q = 0; q < P::NF; ++q)
 #pragma unroll
-    for (int q = 0; q < P::NF; ++q) frag(q, ks, f[q]);
+      for (int p = 0; p < 3; ++p)
+        f[ks][q][p] = lds[p * ROWS * 4 + pl_chunk(rows[q] + r32, 2 * ks + half)];
+  f32x16 big;
 #pragma unroll
-    for (int t = 0; t < SPLIT_TERMS; ++t)
-#pragma unroll
-      for (int j = 0; j < P::NB; ++j)
-        sum[j] = mfma32_bf16(f[P::ia(j)][split_a(t)], f[P::ib(j)][split_b(t)], sum[j]);
+  for (int j = 0; j < P::NB; ++j) {
+    const int ia = P::ia(j), ib = P::ib(j);
+    const f32x16 small = split_small(f[1][ia], f[1][ib], split_small(f[0][ia], f[0][ib], f32x16{}));
+    if (j > 0) split_add(acc[j - 1], big);
+    big = mfma32_bf16(f[1][ia][0], f[1][ib][0], mfma32_bf16(f[0][ia][0], f[0][ib][0], f32x16{}));
+    split_add(acc[j], small);
     __builtin_amdgcn_sched_barrier(0);
   }
-#pragma unroll
-  for (int j = 0; j < P::NB; ++j) acc[j] += sum[j];
+  split_add(acc[P::NB - 1], big);
 }
 
 // Streams the rows of one or two T-tiles of a matrix pair through LDS.
@@ -362,13 +361,12 @@ constexpr bool gram_split() { return DT == DT_F32 && PF == 2; }
 template <int DT, int PF, int ROWS>
 constexpr int stage_chunks() { return ROWS * (gram_split<DT, PF>() ? 12 : 8); }
 
-template <int DT, bool VEC, int PAT, int PF>
+template <int DT, bool VEC, int PAT, int PF, bool SPLIT = gram_split<DT, PF>()>
 __device__ __forceinline__ float gram_item(const GramLayer& L, int b, int T, int ti, int tj, int chunk,
                            u32x4* lds) {
   constexpr int NB = PatNB<PAT>::NB;
   constexpr int ROWS = PatRows<PAT>::ROWS;
   constexpr int NENT = ROWS / 32;  // 16-byte chunks per thread per stage
-  constexpr bool SPLIT = gram_split<DT, PF>();
   using TS = TileStream<DT, VEC>;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -501,6 +499,21 @@ __global__ __launch_bounds__(GR_THREADS, 2) void gram_norm_kernel(GramArgs args)
       part = gram_item<DT, VEC, PAT_D1, 2>(L, b, a.T, ti, tj, chunk, lds);
     else
       part = gram_item<DT, VEC, PAT_D2, 2>(L, b, a.T, ti, tj, chunk, lds);
+    if constexpr (gram_split<DT, 2>()) {
+      // Infinite operands and overflowing products give what the fp32 matrix
+      // cores give: a part that is not finite is computed again on them.
+      const bool bad = __any(!(fabsf(part) <= FLT_MAX));
+      if ((threadIdx.x & 63) == 0) red[w] = bad ? 1.f : 0.f;
+      __syncthreads();
+      const bool again = red[0] + red[1] + red[2] + red[3] != 0.f;
+      __syncthreads();
+      if (again) {
+        if (w < 2)
+          part = gram_item<DT, VEC, PAT_D1, 2, false>(L, b, a.T, ti, tj, chunk, lds);
+        else
+          part = gram_item<DT, VEC, PAT_D2, 2, false>(L, b, a.T, ti, tj, chunk, lds);
+      }
+    }
   } else {
     if (ti != tj)
       part = gram_item<DT, VEC, PAT_OFF, 1>(L, b, a.T, ti, tj, chunk, lds);

@@ -240,3 +240,113 @@ def test_split_sums_on_two_streams_and_in_a_graph():
         torch.cuda.synchronize()
         for grp, w in zip(grps, want):
             assert torch.equal(grp._outs[0], w)
+
+
+@pytest.mark.parametrize("exponent", [0, -100, -125], ids=["ordinary", "small", "near-denormal"])
+def test_fp32_products_are_off_by_two_roundings(exponent):
+    """One token and a factor of 1, so that every output is one product: the plane
+    products that are left out are at most 2^-24 of it, and the kept ones are added with
+    one rounding, 2^-24 again (what cutting the small ones' sum adds is below 2^-30).
+    Values too small for exact bf16 planes (below 2^-110) keep the same bound, up to the
+    outputs' own denormal spacing."""
+    from paper_2609_40335_amd import dpghost as dp
+    g = torch.Generator(device="cuda").manual_seed(10)
+    A = torch.randn(1, 1, 300, generator=g, device="cuda")
+    G = torch.randn(1, 1, 260, generator=g, device="cuda") * 2.0 ** exponent
+    out = torch.zeros(300, 260, device="cuda")
+    dp.dp_clipped_grad_sum(A, G, torch.ones(1, device="cuda"), out)
+    want = A.double().view(-1, 1) * G.double().view(1, -1)
+    err = (out.double() - want).abs() - 2.0 ** -149
+    assert float((err / want.abs()).max()) <= 2.0 ** -23 * 1.02
+
+
+ONE_SIGN = {
+    "softmax": lambda r: torch.softmax(r, -1),
+    "gelu": torch.nn.functional.gelu,
+    "positive": torch.abs,
+    "third": lambda r: torch.full_like(r, 1 / 3),
+}
+
+
+@pytest.mark.parametrize("T", [16, 128, 1024])
+@pytest.mark.parametrize("kinds", [("gelu", "softmax"), ("third", "positive"), ("positive", "positive")],
+                         ids="-".join)
+def test_fp32_sums_of_one_sign(kinds, T):
+    """Operands of one sign, where every cut of a partial sum adds up. A sum of T tokens is n =
+    2 T / 16 additions, each off by at most 2^-24 of the running value, either way: 2^-24
+    / sqrt(3) as a root mean square, times sqrt(n / 3) for a value that grows evenly; and each
+    stage's large products are cut one way, by 2^-24 of them at most. Over the matrix the
+    additions' errors average out of a norm, which keeps twice that cut and the roundings of
+    its own last additions: 1.5e-7 as a root mean square over the examples. (With the plane
+    products on the running accumulator, direct norms were at 2e-7 to 7e-7 for T = 1024.)"""
+    from paper_2609_40335_amd import dpghost as dp
+    B, di, do = 64, 96, 80
+    g = torch.Generator(device="cuda").manual_seed(12)
+    A = ONE_SIGN[kinds[0]](torch.randn(B, T, di, generator=g, device="cuda"))
+    G = ONE_SIGN[kinds[1]](torch.randn(B, T, do, generator=g, device="cuda"))
+    P = per_example(A, G)
+    want = P.square().sum((1, 2))
+    for algo in (dp.DP_NORM_DIRECT,) + ((dp.DP_NORM_GRAM,) if T <= 128 else ()):
+        n2 = torch.zeros(B, device="cuda")
+        dp.dp_ghost_norm_linear(A, G, n2, algo=algo)
+        assert float(((n2.double() - want) / want).square().mean().sqrt()) < 1.5e-7, algo
+    bound = 2.0 ** -24 * (1 + (2 * T / 16 / 9) ** 0.5)
+    for b in range(3):
+        out = torch.zeros(di, do, device="cuda")
+        dp.dp_clipped_grad_sum(A[b:b + 1], G[b:b + 1], torch.ones(1, device="cuda"), out)
+        assert float((out.double() - P[b]).norm() / P[b].norm()) < bound
+
+
+@pytest.mark.parametrize("shape", [(3, 1, 40, 50), (3, 5, 40, 300), (3, 100, 300, 72), (3, 130, 64, 64)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_fp32_infinities_and_overflow(shape):
+    """What fp32 products and sums give: an infinite operand makes infinities of its products'
+    signs, a product too large an infinity, NaN stays NaN, an example with c = 0 is left out;
+    norms of overflowing examples are infinite, the other examples' untouched."""
+    from paper_2609_40335_amd import dpghost as dp
+    B, T, di, do = shape
+    g = torch.Generator(device="cuda").manual_seed(13)
+    A = torch.randn(B, T, di, generator=g, device="cuda")
+    G = torch.randn(B, T, do, generator=g, device="cuda")
+    c = torch.tensor([1.0, 0.5, 0.7], device="cuda")
+    inf = float("inf")
+    cases = {"inf": A.clone(), "overflow": A.clone(), "largest": A.clone(), "nan": A.clone()}
+    cases["inf"][1, 0, 3] = inf
+    cases["overflow"][1] = A[1].abs() * 1e25
+    cases["largest"][1, 0, 5] = 3.4e38     # rounds to infinity in bf16
+    cases["nan"][1, T - 1, 0] = float("nan")
+    for name, X in cases.items():
+        Y = G.clone()
+        if name == "overflow":
+            Y[1] = G[1].abs() * 1e14
+        if name == "largest":
+            Y[1] *= 1e-30
+        want = (per_example(X, Y) * c.double().view(B, 1, 1)).sum(0).float()
+        out = torch.zeros(di, do, device="cuda")
+        dp.dp_clipped_grad_sum(X, Y, c, out)
+        grp = dp.LinearGroup([(X, Y)], [torch.zeros(di, do, device="cuda")])
+        grp.clipped_sum(c)
+        for got in (out, grp._outs[0]):
+            assert torch.equal(got == inf, want == inf), name
+            assert torch.equal(got == -inf, want == -inf), name
+            assert torch.equal(got.isnan(), want.isnan()), name
+            ok = want.isfinite()
+            if ok.any():
+                assert float((got[ok].double() - want[ok].double()).norm()
+                             / want[ok].double().norm()) < 1e-5, name
+        c0 = torch.tensor([1.0, 0.0, 0.7], device="cuda")
+        dp.dp_clipped_grad_sum(X, Y, c0, out)
+        w0 = (per_example(A, G)[[0, 2]] * c0[[0, 2]].double().view(2, 1, 1)).sum(0)
+        assert float((out.double() - w0).norm() / w0.norm()) < 1e-5, name
+        n2w = per_example(A, G).square().sum((1, 2))
+        for algo in (dp.DP_NORM_GRAM, dp.DP_NORM_DIRECT):
+            n2 = torch.zeros(B, device="cuda")
+            dp.dp_ghost_norm_linear(X, Y, n2, algo=algo)
+            for b in (0, 2):
+                assert abs(float(n2[b]) / float(n2w[b]) - 1) < 1e-5, name
+            if name == "overflow":
+                assert float(n2[1]) == inf, algo
+            elif name == "nan":
+                assert bool(n2[1].isnan()), algo
+            elif name == "inf":
+                assert not bool(n2[1].isfinite()), algo
