@@ -50,6 +50,9 @@
 extern "C" {
 #endif
 
+/* The version of what an existing caller relies on: it changes when an entry point, a struct
+ * or a documented result does. Version 3 gained dp_clipped_grad_sum_split_workspace and
+ * dp_clipped_grad_sum_grouped_ws under the same number. */
 #define DP_ABI_VERSION 3
 
 /* Enumerations are int-sized in both languages. Compiled as C++ they have
@@ -254,7 +257,8 @@ dp_status_t dp_clip_factors_scaled2(const float* norm2_a, const float* norm2_b, 
  * c[b] G[b,t,:]. A tied matrix receives both the head and the embedding
  * parts in one buffer: call the head form, then the embedding form with
  * accumulate = 1.
- * Workspace: only the embedding form needs one,
+ * Workspace: only the embedding form uses one (the linear form ignores it;
+ * dp_clipped_grad_sum_grouped_ws takes one for a single layer too),
  * dp_clipped_grad_sum_workspace(B, T, d_out, 1) bytes; limit for it:
  * ceil(log2(V + 1)) + ceil(log2(B*T)) <= 32 (a sort key holds an id
  * clamped to V and a token index; B*T <= 65536 at V = 50257). Up to 16384
@@ -307,8 +311,7 @@ dp_status_t dp_clipped_grad_sum_grouped(const dp_linear_t* layers, float* const*
  * keep at most half of the compute units busy, each of its tiles is computed as
  * 2-8 consecutive K ranges on separate compute units; the fp32 partial tiles go
  * to the workspace and are added in order, so results differ from the call
- * above by fp32 rounding only. The linear form of dp_clipped_grad_sum uses its
- * workspace in the same way. */
+ * above by fp32 rounding only. */
 size_t dp_clipped_grad_sum_split_workspace(const dp_linear_t* layers, int n_layers, int B, int T,
                                            dp_dtype_t dt, int transpose_out);
 dp_status_t dp_clipped_grad_sum_grouped_ws(const dp_linear_t* layers, float* const* outs,

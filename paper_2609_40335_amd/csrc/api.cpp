@@ -1254,8 +1254,8 @@ dp_status_t dp_clipped_grad_sum(const void* A, int64_t lda, const void* G, int64
                                 void* stream) {
   if (!ids) {
     dp_linear_t L{A, lda, d_in, G, ldg, d_out, DP_NORM_AUTO};
-    return dp_clipped_grad_sum_grouped_ws(&L, &out, 1, c, B, T, dt, transpose_out, accumulate,
-                                          workspace, workspace ? workspace_bytes : 0, stream);
+    return dp_clipped_grad_sum_grouped(&L, &out, 1, c, B, T, dt, transpose_out, accumulate,
+                                       stream);
   }
   // Embedding form: A = onehot(ids), d_in = V.
   if (A) return fail(DP_EINVAL, "pass either A or ids, not both");

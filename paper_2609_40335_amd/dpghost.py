@@ -194,6 +194,8 @@ def _on(stream):
 
 def _ws(nbytes: int, device, stream=None) -> torch.Tensor:
     """Scratch of a call on ``stream`` (None: the current one)."""
+    if stream is None:
+        return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
     with _on(stream):
         return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
 
@@ -368,10 +370,12 @@ def dp_clipped_grad_sum(A, G, c, out, ids=None, V: Optional[int] = None,
         desc = (dp_linear_t * 1)(dp_linear_t(pa, lda, d_in, pg, ldg, d_out, DP_NORM_AUTO))
         nbytes = _split_bytes(desc, 1, B, T, dt, transpose_out)
         ws = _ws(nbytes, G.device, stream) if nbytes else None
-        _check(L.dp_clipped_grad_sum(pa, lda, pg, ldg, None, c.data_ptr(), B, T, d_in, d_out, dt,
-                                     int(transpose_out), out.data_ptr(), int(accumulate),
-                                     None if ws is None else ws.data_ptr(),
-                                     0 if ws is None else ws.numel(), _stream(stream)),
+        outs = (ctypes.c_void_p * 1)(out.data_ptr())
+        _check(L.dp_clipped_grad_sum_grouped_ws(desc, outs, 1, c.data_ptr(), B, T, dt,
+                                                int(transpose_out), int(accumulate),
+                                                None if ws is None else ws.data_ptr(),
+                                                0 if ws is None else ws.numel(),
+                                                _stream(stream)),
                "dp_clipped_grad_sum")
         return out
     if A is not None or V is None:

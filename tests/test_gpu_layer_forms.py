@@ -350,3 +350,25 @@ def test_fp32_infinities_and_overflow(shape):
                 assert bool(n2[1].isnan()), algo
             elif name == "inf":
                 assert not bool(n2[1].isfinite()), algo
+
+
+def test_linear_form_leaves_its_workspace_alone():
+    """dp_clipped_grad_sum's linear form takes no workspace: one that a caller passes
+    (the argument serves the embedding form) is not written, whatever its size."""
+    from paper_2609_40335_amd import dpghost as dp
+    B, T, di, do = 6, 160, 300, 264
+    A, G, _ = operands(7, B, T, di, do, torch.bfloat16, 304, 264, 0)
+    c = factors(B)
+    out = torch.zeros(di, do, device="cuda")
+    desc = (dp.dp_linear_t * 1)(dp._layer(A, G))
+    L = dp.lib()
+    nbytes = L.dp_clipped_grad_sum_split_workspace(desc, 1, B, T, dp.DP_BF16, 0)
+    assert nbytes > 0
+    ws = torch.full((nbytes,), 0xAB, dtype=torch.uint8, device="cuda")
+    d = desc[0]
+    st = L.dp_clipped_grad_sum(d.A, d.lda, d.G, d.ldg, None, c.data_ptr(), B, T, di, do, dp.DP_BF16,
+                               0, out.data_ptr(), 0, ws.data_ptr(), ws.numel(), dp._stream(None))
+    assert st == 0
+    assert bool((ws == 0xAB).all())
+    want = (per_example(A, G) * c.double().view(B, 1, 1)).sum(0)
+    assert float((out.double() - want).norm() / want.norm()) < 1e-5
