@@ -529,23 +529,6 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
     __syncthreads();
   }
 
-  // f(value) over this lane's elements inside the matrix.
-  auto each = [&](auto f) __attribute__((always_inline)) {
-    // Rows and columns left in the tile past this lane's first element. Opaque, so
-    // that the elements' masks are not kept from one use to the next.
-    int lim_m = (int)(L.M - m0) - (wm * 128 + (lane >> 5) * 4);
-    int lim_n = (int)(L.N - n0) - (wn * 64 + (lane & 31));
-    asm volatile("" : "+v"(lim_m), "+v"(lim_n));
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bool nin = j * 32 < lim_n;
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          f(nin && i * 32 + (e >> 2) * 8 + (e & 3) < lim_m ? acc[i][j][e] : 0.f);
-      }
-  };
   // The wave's part of the tile on the fp32 matrix cores, from memory. An
   // infinity's planes hold NaN, and where a product overflows, plane products
   // of both signs may: a result that is not finite is computed again with this,
@@ -585,12 +568,21 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
   };
 
   if constexpr (MODE == MODE_SUM) {
-    float z = 0.f, top = 0.f;  // z: NaN if any element is not finite
-    each([&](float v) {
-      z = fmaf(v, 0.f, z);
-      top = fmaxf(top, fabsf(v));
-    });
-    if (__any(z != z) || (!__any(top >= 0x1p-60f) && __any(top > 0.f))) again();
+    // (Blocks that straddle the matrix's last row count whole: what lies past it is
+    // finite, or costs the second pass.)
+    float size = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (m0 + wm * 128 + i * 32 >= L.M) break;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        float t = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) t += fabsf(acc[i][j][e]);
+        if (n0 + wn * 64 + j * 32 + r32 < L.N) size += t;
+      }
+    }
+    if (__any(!(size <= FLT_MAX)) || (!__any(size >= 0x1p-60f) && __any(size > 0.f))) again();
     float* const slice = (float*)lds + w * 32 * EP_LD;
     // The host orders every launch so that the kernel's rows are the output's.
     if (kc < 0)
@@ -602,8 +594,23 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
     float part = 0.f;
 #pragma unroll 1
     for (int pass = 0; pass < 2; ++pass) {
+      // Rows and columns left in the tile past this lane's first element. Opaque, so
+      // that the elements' masks are not kept from one pass to the next.
+      int lim_m = (int)(L.M - m0) - (wm * 128 + (lane >> 5) * 4);
+      int lim_n = (int)(L.N - n0) - (wn * 64 + (lane & 31));
+      asm volatile("" : "+v"(lim_m), "+v"(lim_n));
       part = 0.f;
-      each([&](float v) { part += v * v; });
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const bool nin = j * 32 < lim_n;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const float v = acc[i][j][e];
+            part += (nin && i * 32 + (e >> 2) * 8 + (e & 3) < lim_m) ? v * v : 0.f;
+          }
+        }
       if (pass == 1 || !__any(!(part <= FLT_MAX))) break;
       again();
     }
