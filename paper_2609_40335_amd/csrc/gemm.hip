@@ -318,21 +318,25 @@ __global__ __launch_bounds__(256) void split_fixup_kernel(GemmArgs args) {
 // The fp32 clipped sum and direct norm: split_gemm_kernel. Every fp32 operand
 // is cut exactly into three bf16 planes (split_f32 in common.hpp), and a
 // product becomes six bf16 ones. Six 32x32x16 bf16 MFMAs take 192 cycles where
-// the eight fp32 32x32x2 ones for the same 16 k take 512. A block's products
-// of a stage are summed from zero, the large one (x0 y0) apart from the five
-// small ones, and the VALU adds both sums to the accumulator: the matrix core
-// cuts off, always towards zero, what lies below a fixed distance from the
-// largest term of a sum, and with all six products on the running accumulator
-// direct norms of operands of one sign were up to 6 times further from fp64
-// than with fp32 MFMAs (1.9e-7 for 4.3e-8 at T = 1024, GELU outputs and softmax
-// gradients; 4.1e-8 now). The clipped sums of DistilGPT2 at B = 24, T = 128,
-// V = 50257 unpadded (498 GFLOP): 5165 us on the fp32 MFMAs, 2307 us on the
-// running accumulator, 2950 us here, bound by the matrix core and the VALU
-// alike (256 additions and about 110 conversions per lane and stage beside 48
-// MFMAs). Their error against fp64 is a third of the fp32 MFMAs' (3.2e-7 to
-// 9.5e-7 of normal operands); it is larger only where the products of 16
-// tokens spread over many binary orders and K is short (lognormal operands of
-// sigma 2: norms 2.3e-7 for 1.4e-7 at T = 32, less than theirs from T = 200 on).
+// the eight fp32 32x32x2 ones for the same 16 k take 512. The clipped sums of
+// DistilGPT2 at B = 24, T = 128, V = 50257 unpadded (498 GFLOP): 5165 us on the
+// fp32 MFMAs, 2310 us here.
+//
+// Errors against fp64, beside the fp32 MFMAs' (normal, uniform, GELU, softmax
+// and shifted operands). Clipped sums, all six products on the running
+// accumulator: 0.05 to 0.97 of theirs from K = 3 to 65536 (K = 1024: 1.8e-7 for
+// 5.8e-7, of one sign 7.0e-8 for 4.2e-7); sums of fewer rows are left to the fp32 MFMAs.
+// Direct norms: the matrix core cuts what lies below a fixed distance from the
+// largest term of a sum, always towards zero, and a norm adds that up over the
+// matrix where the additions' other errors average out: on the running accumulator 1.9
+// times theirs (T = 1024, GELU outputs and softmax gradients). There a block's
+// large products (x0 y0) of a stage and its five small ones are summed from
+// zero, apart, and the VALU adds both to the accumulator: 0.8 to 1.1 of theirs
+// (4.0e-8 for 4.3e-8), and 346 us where the running accumulator takes 304 and the fp32
+// MFMAs 485 (four layers 768 -> 3072, B = 24, T = 128). Where the products of 16 tokens
+// spread over many binary orders and K is short, both are larger (lognormal
+// operands of sigma 2, K = 32: sums 1.2e-7 for 1.1e-7, norms 2.4e-7 for
+// 1.4e-7; smaller again from K = 100 and 200 on).
 //
 // Tile 256x256, 16 k per stage, 8 waves of 128x64 as in the bf16 kernel.
 // Waves 0-3 stage X, waves 4-7 Y: a wave takes 8 k rows and 128 columns, a
@@ -347,6 +351,7 @@ __global__ __launch_bounds__(256) void split_fixup_kernel(GemmArgs args) {
 constexpr int SP_PLANE = 2 * GM_BM;         // 16-byte chunks of one plane: two k halves
 constexpr int SP_OP = 3 * SP_PLANE;         // of one operand
 constexpr int SP_STAGE = 2 * SP_OP;         // of one stage
+constexpr int SP_FEW = 2;                   // rows of a sum up to which the planes' error is larger
 static_assert((GM_THREADS / WAVE) * 32 * EP_LD * 4 <= 2 * SP_STAGE * 16, "epilogue slices fit");
 
 // Chunk of column m within a half plane: even columns first, odd ones behind
@@ -480,32 +485,46 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
   const u32x4* const rd_x = lds + half * GM_BM + wm * 64 + sp_slot(r32);
   const u32x4* const rd_y = lds + SP_OP + half * GM_BM + wn * 32 + sp_slot(r32);
   auto compute = [&](int buf) __attribute__((always_inline)) {
-    // The sum of a block's large products is added to its accumulator while the
-    // next block is multiplied. Fences bound how far the reads move up (all at
-    // once, they spill).
+    // The next block row's fragments are read while this one's are multiplied, and
+    // (direct norm) a block's large products are added while the next block's are
+    // multiplied. Fences bound how far the reads move up (all at once, they spill).
     const u32x4* const bx = rd_x + buf * SP_STAGE;
     const u32x4* const by = rd_y + buf * SP_STAGE;
-    u32x4 y[2][3], x[3];
+    u32x4 y[2][3], x[2][3];
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
+      x[0][p] = bx[p * SP_PLANE];
       y[0][p] = by[p * SP_PLANE];
       y[1][p] = by[p * SP_PLANE + 16];
     }
     f32x16 big;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int i = q >> 1, j = q & 1;
-      if (j == 0) {
+    for (int i = 0; i < 4; ++i) {
+      const u32x4(&xi)[3] = x[i & 1];
+      if (i < 3) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p) x[p] = bx[p * SP_PLANE + i * 16];
+        for (int p = 0; p < 3; ++p) x[(i + 1) & 1][p] = bx[p * SP_PLANE + (i + 1) * 16];
       }
-      const f32x16 small = split_small(x, y[j], f32x16{});
-      if (q > 0) split_add(acc[(q - 1) >> 1][(q - 1) & 1], big);
-      big = mfma32_bf16(x[0], y[j][0], f32x16{});
-      split_add(acc[i][j], small);
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (MODE == MODE_SUM) {
+#pragma unroll
+        for (int t = 0; t < SPLIT_TERMS; ++t)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = mfma32_bf16(xi[split_a(t)], y[j][split_b(t)], acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const f32x16 small = split_small(xi, y[j], f32x16{});
+          if (j == 1) split_add(acc[i][0], big);
+          else if (i > 0) split_add(acc[i - 1][1], big);
+          big = mfma32_bf16(xi[0], y[j][0], f32x16{});
+          split_add(acc[i][j], small);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
-    split_add(acc[3][1], big);
+    if constexpr (MODE == MODE_NORM) split_add(acc[3][1], big);
   };
 
   load();
@@ -582,7 +601,9 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
         if (n0 + wn * 64 + j * 32 + r32 < L.N) size += t;
       }
     }
-    if (__any(!(size <= FLT_MAX)) || (!__any(size >= 0x1p-60f) && __any(size > 0.f))) again();
+    if (rows <= SP_FEW || __any(!(size <= FLT_MAX)) ||
+        (!__any(size >= 0x1p-60f) && __any(size > 0.f)))
+      again();
     float* const slice = (float*)lds + w * 32 * EP_LD;
     // The host orders every launch so that the kernel's rows are the output's.
     if (kc < 0)

@@ -275,7 +275,8 @@ def test_fp32_sums_of_one_sign(kinds, T):
     """Operands of one sign, where every cut of a partial sum adds up. A sum of T tokens is n =
     2 T / 16 additions, each off by at most 2^-24 of the running value, either way: 2^-24
     / sqrt(3) as a root mean square, times sqrt(n / 3) for a value that grows evenly; and each
-    stage's large products are cut one way, by 2^-24 of them at most. Over the matrix the
+    stage's products are cut one way, by 2^-24 of them at most. (Clipped sums add six times a
+    stage, the small products among them: no more than twice as many roundings.) Over the matrix the
     additions' errors average out of a norm, which keeps twice that cut and the roundings of
     its own last additions: 1.5e-7 as a root mean square over the examples. (With the plane
     products on the running accumulator, direct norms were at 2e-7 to 7e-7 for T = 1024.)"""
