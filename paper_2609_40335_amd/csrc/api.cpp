@@ -416,13 +416,12 @@ size_t sum_split_bytes(const std::vector<GemmEntry>& entries, int B, int T, dp_d
 // mode 0: clipped sum (c, out); mode 1: direct norm (ws, slots). A clipped sum
 // given `part` (part_bytes) splits the tail of its launches.
 dp_status_t run_gemm(const std::vector<GemmEntry>& entries, int mode, int B, int T, dp_dtype_t dt,
-                     const float* c, float* ws, int64_t slots, int transpose, const NoiseCfg& nz,
+                     const float* c, float* ws, int64_t slots, const NoiseCfg& nz,
                      hipStream_t s, float* part = nullptr, size_t part_bytes = 0,
                      float* store = nullptr) {
   for (const auto& [vec, sel] : gemm_launches(entries)) {
     dpg::GemmArgs a{};
     a.B = B; a.T = T; a.c = c; a.ws = ws; a.slots = (int32_t)slots;
-    a.transpose = transpose;
     a.store = store;
     a.noise = nz.on ? 1 : 0;
     a.sigma_c = nz.sigma_c; a.inv_b = nz.inv_b; a.step = nz.step; a.seed = nz.seed;
@@ -719,7 +718,7 @@ dp_status_t norm_bias_grouped(const dp_linear_t* layers, float* const* bias_grad
   float* ws = static_cast<float*>(workspace);
   st = run_gram(p, B, T, dt, ws, s);
   if (st != DP_OK) return st;
-  st = run_gemm(p.direct, 1, B, T, dt, nullptr, ws, p.slots, 0, NoiseCfg{}, s);
+  st = run_gemm(p.direct, 1, B, T, dt, nullptr, ws, p.slots, NoiseCfg{}, s);
   if (st != DP_OK) return st;
   float* vws = reinterpret_cast<float*>(static_cast<char*>(workspace) + norm_bytes);
   if (!vp.e.empty()) {
@@ -965,7 +964,7 @@ dp_status_t dp_clipped_grad_sum_grouped_ws(const dp_linear_t* layers, float* con
     plan_sum(layers[i], transpose_out, dt, outs[i], entries);
     entries.back().acc = accumulate ? 1 : 0;
   }
-  return run_gemm(entries, 0, B, T, dt, c, nullptr, 0, 0, NoiseCfg{}, as_stream(stream),
+  return run_gemm(entries, 0, B, T, dt, c, nullptr, 0, NoiseCfg{}, as_stream(stream),
                   static_cast<float*>(workspace), workspace ? workspace_bytes : 0);
 }
 
@@ -1037,7 +1036,7 @@ dp_status_t dp_clipped_grad_sum_noised_grouped_ws(const dp_linear_t* layers, flo
   nz.inv_b = B_norm > 0 ? (float)(1.0 / (double)B_norm) : 1.f;
   nz.seed = seed;
   nz.step = (uint32_t)step;
-  return run_gemm(entries, 0, B, T, dt, c, nullptr, 0, 0, nz, as_stream(stream),
+  return run_gemm(entries, 0, B, T, dt, c, nullptr, 0, nz, as_stream(stream),
                   static_cast<float*>(workspace), workspace ? workspace_bytes : 0);
 }
 
@@ -1106,7 +1105,7 @@ dp_status_t dp_ghost_norm_linear_store(const dp_linear_t* layers, int n_layers, 
   hipStream_t s = as_stream(stream);
   float* tiles_f = static_cast<float*>(store);
   float* ws = reinterpret_cast<float*>(static_cast<char*>(store) + store_tiles_bytes(B, tiles));
-  st = run_gemm(entries, 1, B, T, dt, nullptr, ws, tiles, 0, NoiseCfg{}, s, nullptr, 0, tiles_f);
+  st = run_gemm(entries, 1, B, T, dt, nullptr, ws, tiles, NoiseCfg{}, s, nullptr, 0, tiles_f);
   if (st != DP_OK) return st;
   return hip_status(dpg::launch_finish_rows(ws, B, (int)tiles, norm2, accumulate, 1.f, s),
                     "finish launch");

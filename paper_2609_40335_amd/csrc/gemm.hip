@@ -51,19 +51,10 @@ __device__ __forceinline__ void tile_of(const GemmLayer& L, uint32_t rel, int& m
   }
 }
 
-// Writes (or adds) one 256x256 output tile: each wave's 4x2 32x32 blocks at
-// rows m0 + wm*128 + i*32, columns n0 + wn*64 + j*32. In a 32x32 block, lane l
-// holds column l%32 and, for accumulator e, row (e/4)*8 + (l/32)*4 + e%4.
-// Stores bypass L2 residency (the output is written once) so that they do
-// not evict operand rows.
-//
-// With the Gaussian mechanism fused (a.noise): value = (prior + sum +
-// sigma_c * z) * inv_b, where z is the standard normal the noise generator
-// assigns to the element's row-major index in the output tensor (row length
-// M when transposed, N otherwise), i.e. the draw dp_add_noise would add to
-// that element. In the transposed layout a lane's 4 accumulators e = 4g..4g+3
-// are 4 consecutive elements of one output row starting at a multiple of 4,
-// so one Philox block serves them when the row length is a multiple of 4.
+// The Gaussian mechanism, where a clipped sum fuses it (a.noise): value = (prior +
+// sum + sigma_c * z) * inv_b, where z is the standard normal the noise generator
+// assigns to the element's row-major index in the output tensor, i.e. the draw
+// dp_add_noise would add to that element.
 __device__ __forceinline__ float noise_at(const GemmArgs& a, uint32_t tid, uint64_t j) {
   float z[4];
   gauss4(j >> 2, a.seed, tid, a.step, z);
@@ -86,9 +77,17 @@ __device__ __forceinline__ void noise4_at(const GemmArgs& a, uint32_t tid, uint6
   }
 }
 
-__device__ __forceinline__ void store_tile(const GemmArgs& a, const GemmLayer& L, int64_t m0,
-                                           int64_t n0, int wm, int wn, int lane,
-                                           f32x16 (&acc)[4][2], bool transposed) {
+// Writes (or adds) one 256x256 tile of an output stored transposed, out[n][m]
+// (row length M; sums from a gradient store only): each wave's 4x2 32x32
+// blocks at rows m0 + wm*128 + i*32, columns n0 + wn*64 + j*32. In a 32x32
+// block, lane l holds column l%32 and, for accumulator e, row (e/4)*8 +
+// (l/32)*4 + e%4, so its 4 accumulators e = 4g..4g+3 are 4 consecutive elements of one
+// output row starting at a multiple of 4, and one Philox block serves them when the row
+// length is a multiple of 4. Stores bypass L2 residency (the output is
+// written once) so that they do not evict operand rows.
+__device__ __forceinline__ void store_tile_transposed(const GemmArgs& a, const GemmLayer& L,
+                                                      int64_t m0, int64_t n0, int wm, int wn,
+                                                      int lane, f32x16 (&acc)[4][2]) {
   float* out = L.out;
   const int64_t ldo = L.ldo;
   const bool accum = L.accumulate != 0;
@@ -97,63 +96,41 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const GemmLayer& L
   const int mw = (int)m0 + wm * 128 + (lane >> 5) * 4;  // row of e = 0 in block i = 0
   const int nw = (int)n0 + wn * 64 + (lane & 31);         // column in block j = 0
   const bool full = m0 + GM_BM <= L.M && n0 + GM_BN <= L.N;
-  if (transposed) {
-    // out[n][m]: the 4 accumulators e = 4g..4g+3 are 4 consecutive rows m.
-    const bool vec4 = full && (ldo & 3) == 0 && (((uintptr_t)out) & 15) == 0 &&
-                      (!noise || (L.M & 3) == 0);
+  const bool vec4 = full && (ldo & 3) == 0 && (((uintptr_t)out) & 15) == 0 &&
+                    (!noise || (L.M & 3) == 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int n = nw + j * 32;
+    for (int j = 0; j < 2; ++j) {
+      const int n = nw + j * 32;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int m = mw + i * 32 + g * 8;
-          float* p = out + (int64_t)n * ldo + m;
-          if (vec4) {
-            f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
-                       acc[i][j][4 * g + 3]};
-            if (accum) v += *(const f32x4*)p;
-            if (noise) {
-              float z[4];
-              gauss4(((uint64_t)n * (uint64_t)L.M + (uint64_t)m) >> 2, a.seed, tid, a.step, z);
+      for (int g = 0; g < 4; ++g) {
+        const int m = mw + i * 32 + g * 8;
+        float* p = out + (int64_t)n * ldo + m;
+        if (vec4) {
+          f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
+                     acc[i][j][4 * g + 3]};
+          if (accum) v += *(const f32x4*)p;
+          if (noise) {
+            float z[4];
+            gauss4(((uint64_t)n * (uint64_t)L.M + (uint64_t)m) >> 2, a.seed, tid, a.step, z);
 #pragma unroll
-              for (int r = 0; r < 4; ++r) v[r] = (v[r] + a.sigma_c * z[r]) * a.inv_b;
+            for (int r = 0; r < 4; ++r) v[r] = (v[r] + a.sigma_c * z[r]) * a.inv_b;
+          }
+          __builtin_nontemporal_store(v, (f32x4*)p);
+        } else if (n < L.N) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (m + r < L.M) {
+              float v = (accum ? p[r] : 0.f) + acc[i][j][4 * g + r];
+              if (noise)
+                v = (v + a.sigma_c * noise_at(a, tid, (uint64_t)n * (uint64_t)L.M + m + r)) *
+                    a.inv_b;
+              p[r] = v;
             }
-            __builtin_nontemporal_store(v, (f32x4*)p);
-          } else if (n < L.N) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (m + r < L.M) {
-                float v = (accum ? p[r] : 0.f) + acc[i][j][4 * g + r];
-                if (noise)
-                  v = (v + a.sigma_c * noise_at(a, tid, (uint64_t)n * (uint64_t)L.M + m + r)) *
-                      a.inv_b;
-                p[r] = v;
-              }
-          }
         }
       }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int n = nw + j * 32;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int m = mw + i * 32 + (e >> 2) * 8 + (e & 3);
-          float* p = out + (int64_t)m * ldo + n;
-          if (full || (m < L.M && n < L.N)) {
-            float v = (accum ? *p : 0.f) + acc[i][j][e];
-            if (noise)
-              v = (v + a.sigma_c * noise_at(a, tid, (uint64_t)m * (uint64_t)L.N + n)) * a.inv_b;
-            if (full) __builtin_nontemporal_store(v, p);
-            else *p = v;
-          }
-        }
-      }
-  }
+    }
 }
 
 // Row-major store of one tile through LDS, for the non-transposed layout
@@ -1104,8 +1081,7 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
     // Chunks past the matrix's columns read the row's padding or the next
     // row, and only feed outputs that are not stored; what must not happen is
     // a read past the matrix's end. `tight`: some chunk of these 8 rows would.
-    // (As a signed offset from the end back: the tile's reach past its first
-    // row's start, and one lane chunk's.)
+    // (reach: from this wave's first row to the end of the tile in its eighth.)
     const uint64_t mend = uniform64(gbase + (uint64_t)K * ld_bytes);
     const uint64_t col_b = uniform64((uint64_t)col0 * 2);
     const uint64_t reach = 7ull * ld_u + col_b + GM_BM * 2;
@@ -1285,8 +1261,6 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
       float* slice = (float*)ring_raw + w * 32 * EP_LD;
       store_partial(a.part + ((size_t)(item - a.n_full) * a.ksplit + kc) * (GM_BM * GM_BN),
                     wm, wn, lane, acc, slice);
-    } else if (a.transpose) {
-      store_tile(a, L, m0, n0, wm, wn, lane, acc, true);
     } else {
       // The ring is free once every wave is past its last read of it.
       __syncthreads();
@@ -1362,7 +1336,7 @@ __global__ __launch_bounds__(GM_THREADS) void store_sum_kernel(GemmArgs args) {
     }
   }
   if (L.store_transpose) {
-    store_tile(a, L, m0, n0, wm, wn, lane, acc, true);
+    store_tile_transposed(a, L, m0, n0, wm, wn, lane, acc);
   } else {
     float* slice = (float*)stage + w * 32 * EP_LD;
     store_tile_rows(a, L, m0, n0, wm, wn, lane, acc, slice);

@@ -98,7 +98,7 @@ constexpr int GM_MAX_LAYERS = 52;   // layers per launch (kernel arguments stay 
 struct GemmLayer {
   const void* X;        // [K rows, ldx]
   const void* Y;        // [K rows, ldy]
-  float* out;           // clipped sum: [M, ldo] or transposed [N, ldo]
+  float* out;           // clipped sum: [M, ldo] (from a gradient store also transposed, [N, ldo])
   union {
     int64_t ldx;          // row stride of X in elements
     int64_t store_slot;   // sum from a gradient store (X, Y unread): first tile slot
@@ -123,7 +123,6 @@ struct GemmArgs {
   int32_t n_layers;
   int32_t B, T;
   uint32_t n_items;
-  int32_t transpose;    // clipped sum: output layout
   const float* c;       // clipped sum: per-example scale [B]
   float* ws;            // direct norm: [B, slots]
   int32_t slots;
