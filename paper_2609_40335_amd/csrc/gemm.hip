@@ -625,8 +625,8 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
 }
 
 // ---------------------------------------------------------------------------
-// Direct-load kernel for the bf16 clipped sum and direct norm. In its PLAIN, BIG
-// and RAGGED forms (16-byte aligned rows; see GemmForm) nothing is staged
+// Direct-load kernel for the bf16 clipped sum and direct norm. In its PLAIN, BIG,
+// RAGGED and SCALED forms (16-byte aligned rows; see GemmForm) nothing is staged
 // through VGPRs; the STAGED and ROWS forms load through registers further down.
 //
 // Global rows go straight into LDS through buffer loads that write LDS
@@ -665,7 +665,11 @@ __global__ __launch_bounds__(GM_THREADS) void split_gemm_kernel(GemmArgs args) {
 // waits behind the fragment reads. Scaling is on the fp32 accumulators:
 // rescaled by c_prev / c_next at example boundaries and by the last factor at the
 // end, examples with c = 0 skipped (so that inf or NaN in their rows adds
-// nothing). In the direct norm the example boundary instead squares and sums
+// nothing). The SCALED form multiplies a wave's Y fragments by their rows' factors
+// instead, in the memory phase (4 fragments of 12: 80 VALU instructions beside
+// the other group's 16 MFMAs): sums of 3072 tokens in examples of 21 (twelve layers 768 ->
+// 3072) 217 us, 401 with the rows scaled on their way through registers, loaded
+// one stage ahead only. In the direct norm the example boundary instead squares and sums
 // each wave's part of the tile (and writes the tile to the gradient store,
 // if there is one), then clears the accumulators for the next example.
 constexpr int DL_BK = DL_SUM_BK;            // k rows per stage
@@ -731,12 +735,16 @@ template <int MODE, int FORM>
 __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
   constexpr bool BIG = FORM == FORM_BIG;
   constexpr bool STAGED = FORM == FORM_STAGED || FORM == FORM_ROWS;  // through registers
-  constexpr bool WHOLE = FORM == FORM_PLAIN || FORM == FORM_BIG;     // T a multiple of DL_BK
-  constexpr bool ROWS = FORM == FORM_ROWS;
+  constexpr bool SCALED = FORM == FORM_SCALED;
+  constexpr bool ROWS = FORM == FORM_ROWS || SCALED;                 // stages over all rows
+  // Stages whose rows follow one another through the batch, loaded straight into LDS.
+  constexpr bool WHOLE = FORM == FORM_PLAIN || FORM == FORM_BIG || SCALED;
   const GemmArgs& a = *(const GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   (void)args;
   __shared__ __attribute__((aligned(1024))) char ring_raw[DL_NS * DL_STB];
   __shared__ float cs[DL_MAXB];
+  // SCALED: each wave's row factors of the stages with even and odd index.
+  __shared__ __attribute__((aligned(16))) float row_c[SCALED ? GM_THREADS / WAVE : 1][2][DL_BK];
   lds_char_t* ring = (lds_char_t*)(lds_void_t*)ring_raw;
 
   // Whole tiles come first (spread over the XCDs); the K ranges of the split
@@ -913,7 +921,7 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
   // A batch of more examples than the table holds reads the factors of the
   // others from memory.
   auto factor = [&](int e) {
-    if (WHOLE || e < DL_MAXB) return cs[e];
+    if ((WHOLE && !SCALED) || e < DL_MAXB) return cs[e];
     float x = a.c[e];
     // Opaque: merged with the other load it would be one load through a
     // generic pointer, whose wait drains the ring.
@@ -1058,6 +1066,57 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
   };
+  // SCALED. A lane looks up the factor of row lane % 32 of a stage, one stage before
+  // its wave reads that stage's fragments, and leaves it in the wave's own slot of LDS.
+  // The example of row r_sc + x is e_sc + x / T, and x / T = hi32(x * rcpT)
+  // for the x < T + DL_BK here (T <= 2 DL_BK).
+  const uint32_t rcp_sc = SCALED ? 0xFFFFFFFFu / (uint32_t)nT + 1u : 0u;
+  auto over_T = [&](int x) { return nT == 1 ? x : (int)__umulhi((uint32_t)x, rcp_sc); };
+  int e_sc = SCALED ? (int)(k_begin / nT) : 0;
+  int r_sc = SCALED ? (int)(k_begin - (int64_t)e_sc * nT) : 0;
+  bool left_out[2] = {false, false};  // some row of the stage has factor 0
+  auto look_up = [&](int s) __attribute__((always_inline)) {
+    const float c = factor(min(e_sc + over_T(r_sc + (lane & 31)), nB - 1));
+    row_c[SCALED ? w : 0][s & 1][lane & 31] = c;
+    left_out[s & 1] = __any(c == 0.f);
+    const int x = r_sc + DL_BK, de = over_T(x);
+    e_sc += de;
+    r_sc = x - de * nT;
+  };
+  // Multiplies stage s's Y fragments by their rows' factors. Where an example is left
+  // out, its rows are zeroed in both operands (0 * inf would be NaN).
+  auto scale = [&](int s, u32x4 (&f)[12]) __attribute__((always_inline)) {
+    const float* rc = row_c[SCALED ? w : 0][s & 1] + 8 * (lane >> 5);
+    f32x4 c[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) c[h][q] = *(const f32x4*)(rc + 16 * h + 4 * q);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const f32x4& ck = c[h][k >> 1];
+          const uint32_t v = f[6 * h + 4 + j][k];
+          const f32x2 x = {__uint_as_float(v << 16) * ck[2 * (k & 1)],
+                           __uint_as_float(v & 0xFFFF0000u) * ck[2 * (k & 1) + 1]};
+          f[6 * h + 4 + j][k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+        }
+    if (left_out[s & 1]) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const f32x4& ck = c[h][k >> 1];
+          const uint32_t keep = (ck[2 * (k & 1)] == 0.f ? 0u : 0xFFFFu) |
+                                (ck[2 * (k & 1) + 1] == 0.f ? 0u : 0xFFFF0000u);
+#pragma unroll
+          for (int q = 0; q < 6; ++q) f[6 * h + q][k] &= keep;
+        }
+    }
+  };
   // Phase boundary; nothing is scheduled across it.
   auto bar = [&]() {
     __builtin_amdgcn_sched_barrier(0);
@@ -1128,7 +1187,7 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
     };
     Cursor wr_at = ld_at;
     // ROWS: example and row within it of this wave's first row of the next
-    // stage to write; row r0w + j lies (r0w + j) / T examples on, and
+    // stage to write; row r_wr + j lies (r_wr + j) / T examples on, and
     // x / T = hi32(x * rcpT) for the x < T + DL_BK here (T <= 2 DL_BK).
     int e_wr = ROWS ? (int)((k_begin + wq * 8) / a.T) : 0;
     int r_wr = ROWS ? (int)((k_begin + wq * 8) - (int64_t)e_wr * a.T) : 0;
@@ -1218,14 +1277,23 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
       for (int t = 0; t < DL_LOADS; ++t) issue(p, t);
     wait_vmcnt<DL_LOADS * (DL_NS - 1)>();
     bar();  // stage 0 has landed, the factor table is filled
-    if constexpr (MODE == MODE_SUM) c_nx = factor(min(e0, nB - 1));
+    if constexpr (MODE == MODE_SUM && !ROWS) c_nx = factor(min(e0, nB - 1));
+    if constexpr (SCALED) look_up(0);
     rd(0, fr);
+    if constexpr (SCALED) {
+      scale(0, fr);
+      look_up(1);
+    }
     enter(0);
     for (int s = 0; s < nS; ++s) {
       compute(fr);
       wait_vmcnt<DL_LOADS * (DL_NS - 2)>();
       bar();
       rd_issue(s + 1, s + DL_NS, fr);  // past the last stage: reads an unused slot
+      if constexpr (SCALED) {
+        scale(s + 1, fr);
+        look_up(s + 2);
+      }
       if (s + 1 < nS) enter(s + 1);
       bar();
     }
@@ -1236,9 +1304,14 @@ __global__ __launch_bounds__(GM_THREADS) void dl_gemm_kernel(GemmArgs args) {
       for (int t = 0; t < DL_LOADS; ++t) issue(p, t);
     wait_vmcnt<DL_LOADS * (DL_NS - 2)>();
     bar();
-    if constexpr (MODE == MODE_SUM) c_nx = factor(min(e0, nB - 1));
+    if constexpr (MODE == MODE_SUM && !ROWS) c_nx = factor(min(e0, nB - 1));
+    if constexpr (SCALED) look_up(0);
     for (int s = 0; s < nS; ++s) {
       rd_issue(s, s + DL_NS - 1, fr);
+      if constexpr (SCALED) {
+        scale(s, fr);
+        look_up(s + 1);
+      }
       enter(s);
       wait_vmcnt<DL_LOADS * (DL_NS - 2)>();
       bar();
@@ -1362,7 +1435,10 @@ static void launch_dl(const GemmArgs& a, int form, uint32_t grid, hipStream_t s)
   } else if (form == FORM_STAGED) {
     hipLaunchKernelGGL((dl_gemm_kernel<MODE, FORM_STAGED>), g, blk, 0, s, a);
   } else if constexpr (MODE == MODE_SUM) {
-    hipLaunchKernelGGL((dl_gemm_kernel<MODE, FORM_ROWS>), g, blk, 0, s, a);
+    if (form == FORM_ROWS)
+      hipLaunchKernelGGL((dl_gemm_kernel<MODE, FORM_ROWS>), g, blk, 0, s, a);
+    else
+      hipLaunchKernelGGL((dl_gemm_kernel<MODE, FORM_SCALED>), g, blk, 0, s, a);
   }
 }
 

@@ -160,19 +160,24 @@ static_assert(sizeof(GemmArgs) <= 4096, "kernel arguments must stay within 4 KiB
 //  RAGGED: 16-byte rows, any T: an example's last stage may be short; its
 //          missing rows read as zeros.
 //  STAGED: rows of any alignment, any T, loaded through registers.
-//  ROWS:   (clipped sum) stages run over the batch's rows without regard to
-//          examples, and X's rows are scaled while staged (c_i A rounds to
-//          bf16). For short examples, whose padding to whole stages would cost
-//          more: ROWS_NUM / ROWS_DEN is the measured ratio of a ROWS stage's
-//          time to a RAGGED one's.
-enum GemmForm { FORM_PLAIN = 0, FORM_BIG, FORM_RAGGED, FORM_STAGED, FORM_ROWS };
+//  SCALED, ROWS: (clipped sum) stages run over the batch's rows without regard to
+//          examples, and one operand's rows are scaled by their examples' factors, which
+//          rounds c_i A (or c_i G) to bf16: SCALED (16-byte rows) loads like PLAIN
+//          and scales the fragments, ROWS loads like STAGED and scales what it stages. For
+//          short examples, whose padding to whole stages would cost more than ROWS_NUM /
+//          ROWS_DEN of their rows. By time alone they would pay earlier; the line is where it is
+//          because the other forms scale in fp32 (error 3e-7 where these have 1.3e-3). Twelve
+//          layers 768 -> 3072, 3072 tokens, us: T = 21: 217 SCALED, 353 RAGGED; 404 ROWS,
+//          592 STAGED (unaligned); T = 22: 217, 337; 404, 565; T = 42: 217, 271; 404,
+//          489; T = 43: 217, 255; 404, 477.
+enum GemmForm { FORM_PLAIN = 0, FORM_BIG, FORM_RAGGED, FORM_STAGED, FORM_ROWS, FORM_SCALED };
 constexpr int DL_SUM_BK = 32;
 constexpr int DL_SUM_MAXB = 4096;  // clip factors held in LDS
 constexpr int ROWS_NUM = 3, ROWS_DEN = 2;
 inline int sum_form(bool vec, int T, int B) {
   if (T % DL_SUM_BK == 0) return !vec ? FORM_STAGED : B <= DL_SUM_MAXB ? FORM_PLAIN : FORM_RAGGED;
   const int64_t padded = (int64_t)((T + DL_SUM_BK - 1) / DL_SUM_BK) * DL_SUM_BK;
-  if (padded * ROWS_DEN > (int64_t)T * ROWS_NUM) return FORM_ROWS;
+  if (padded * ROWS_DEN > (int64_t)T * ROWS_NUM) return vec ? FORM_SCALED : FORM_ROWS;
   return vec ? FORM_RAGGED : FORM_STAGED;
 }
 inline int norm_form(bool vec, int T) {
@@ -188,7 +193,8 @@ constexpr int SP_BK = 16;          // K rows per stage of the fp32 kernel
 inline int sum_stages(int dt, bool vec, int T, int B) {
   const int64_t K = (int64_t)B * T;
   if (dt != DT_BF16) return (int)((K + SP_BK - 1) / SP_BK);
-  if (sum_form(vec, T, B) == FORM_ROWS) return (int)((K + DL_SUM_BK - 1) / DL_SUM_BK);
+  const int form = sum_form(vec, T, B);
+  if (form == FORM_ROWS || form == FORM_SCALED) return (int)((K + DL_SUM_BK - 1) / DL_SUM_BK);
   return (int)((int64_t)B * ((T + DL_SUM_BK - 1) / DL_SUM_BK));
 }
 
