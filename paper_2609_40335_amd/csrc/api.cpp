@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <limits>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -179,12 +180,13 @@ void plan_sum(const dp_linear_t& L, int transpose_out, dp_dtype_t dt, float* out
 // KG_SPLIT and at least KG_MIN features wide (whole stages); among those
 // counts, the one whose launch (this layer's items plus `other` items of the
 // same kernel) fills the last round of `slots` concurrent workgroups best,
-// the fewest chunks on a tie (each chunk re-reads A).
+// the fewest chunks on a tie (each chunk re-reads A). A launch that cannot fill
+// one round takes the most chunks: its time is that of one item.
 int pick_chunks(int64_t width, int ks, int64_t items_per_chunk, int64_t other, int64_t slots) {
   const int64_t nc_lo = ceil_div(width, KG_SPLIT);
   const int64_t nc_hi = std::max(nc_lo, ceil_div(width, KG_MIN));
   int64_t best = nc_lo;
-  double best_idle = 2.0;
+  double best_idle = std::numeric_limits<double>::infinity();
   for (int64_t nc = nc_lo; nc <= nc_hi; ++nc) {
     const int64_t kg = ceil_div(ceil_div(width, nc), ks) * ks;
     const int64_t eff = ceil_div(width, kg);

@@ -488,3 +488,16 @@ def test_noalloc_plan_falls_back_to_fewer_partials(L):
     st = L.dp_ghost_norm_linear_bias_grouped_noalloc(arr, None, 500, 1, 4, D.DP_F32, 1 << 40, 0,
                                                      None)
     assert L.dp_status_string(st) == b"HIP error", L.dp_last_error()
+
+
+@pytest.mark.parametrize("dt,ks", [(D.DP_BF16, 64), (D.DP_F32, 32)], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("Bn", [1, 4, 8, 10])
+def test_wide_layer_of_few_examples_takes_narrow_chunks(L, dt, ks, Bn):
+    """A G range longer than 4096 features in a launch that cannot occupy every workgroup slot
+    once: the time is that of one item, so the chunks are the narrowest allowed (1024
+    features, whole stages), however small the launch is beside the slots."""
+    one = (D.dp_linear_t * 1)(_lin(d_in=256, lda=256, d_out=20000, ldg=20000, algo=D.DP_NORM_GRAM))
+    nc = -(-20000 // (-(-(-(-20000 // 20)) // ks) * ks))
+    assert nc >= 19
+    want = (Bn * nc * 4 + 255) // 256 * 256
+    assert L.dp_ghost_norm_linear_workspace(one, 1, Bn, 32, dt) == want
