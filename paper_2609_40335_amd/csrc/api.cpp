@@ -201,34 +201,40 @@ int pick_chunks(int64_t width, int ks, int64_t items_per_chunk, int64_t other, i
 // a Gram launch whose items would not occupy every workgroup slot once: an
 // item's stages are a serial chain (about 0.5 us each), so such a launch takes
 // as long as its longest item. Narrower chunks shorten it and fill idle
-// compute units, and each one repeats the layer's A stages. The choice
-// minimises max(longest item, stages per workgroup slot), with GRAM_FILL
-// stages per item for filling the ring and reducing the partials; nothing is gained
-// below the length of the other layers' items (other_len). (d_in = 768,
-// d_out = 3072, B = 24, T = 128: the norm took 34 us of 109 for norm and sum,
-// 12 of 87 with it.) A launch of a full round or more keeps its items: each
-// chunk's repeated A stages then cost more than the shorter tail gains.
+// compute units, and each one repeats the layer's A stages. The choice is the shortest
+// longest item among the widths whose items still run in one round, the widest on a
+// tie; nothing is gained below the length of the other layers' items (other_len).
+// (d_in = 768, d_out = 3072, B = 24, T = 128: the norm took 34 us of 109 for norm and
+// sum, 12 of 87 with it.) A launch of more than one round keeps its items: each
+// chunk's repeated A stages cost more than the shorter tail gains, and as
+// an XCD runs consecutive items, the longest layers' items pile up on one (norms and biases of
+// GPT-2's layers in fp32, B = 1, T = 160, 648 chunked items on 256 slots: 337 us whole, 520 so cut).
+// GRAM_FILL: an item's length counts that many stages for filling the ring and
+// reducing the partials. (Anything from 0 to 24 measured within 3 % over ten launches, save one
+// that took 29 us up to 6 and 23 from 12 on.) Where no width fits one round and a range is
+// longer than KG_SPLIT features (`wide` stages), ranges are cut at the widest one all the
+// same, as those of a wide G always are.
 constexpr int GRAM_FILL = 6;
 struct GramShape {
   int64_t items, nx, ny;  // items per chunk; stages of A, of G
 };
 int few_items_chunk(const std::vector<GramShape>& v, int64_t other, int64_t other_len,
-                    int64_t slots) {
+                    int64_t slots, int64_t wide) {
   int64_t items = other;
   for (const GramShape& g : v) items += g.items;
   if (v.empty() || items >= slots) return 0;
   int best = 0;
-  double best_cost = 0;
+  int64_t best_len = 0;
   for (int q : {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
-    int64_t longest = other_len, total = 0;
+    int64_t longest = other_len, total = other;
     for (const GramShape& g : v) {
-      const int64_t len = g.nx + std::min<int64_t>(q, g.ny) + GRAM_FILL;
-      longest = std::max(longest, len);
-      total += g.items * ceil_div(g.ny, q) * len;
+      longest = std::max(longest, g.nx + std::min<int64_t>(q, g.ny) + GRAM_FILL);
+      total += g.items * ceil_div(g.ny, q);
     }
-    const double cost = std::max((double)longest, (double)total / (double)(slots - other));
-    if (best == 0 || cost <= best_cost) { best = q; best_cost = cost; }
+    if (total <= slots && (best == 0 || longest <= best_len)) { best = q; best_len = longest; }
   }
+  if (best == 0 && std::any_of(v.begin(), v.end(), [&](const GramShape& g) { return g.ny > wide; }))
+    best = 64;
   return best;
 }
 
@@ -275,7 +281,7 @@ NormPlan plan_norm(const dp_linear_t* layers, int n, int B, int T, dp_dtype_t dt
   }
   int few[2];  // stages per G chunk where a launch is short of items, else 0
   for (int v = 0; v < 2; ++v)
-    few[v] = lean ? 0 : few_items_chunk(shapes[v], wide_items[v], wide_len[v], slots);
+    few[v] = lean ? 0 : few_items_chunk(shapes[v], wide_items[v], wide_len[v], slots, KG_SPLIT / ks);
   for (int i = 0; i < n; ++i) {
     const dp_linear_t& L = layers[i];
     float* const bg = bias ? bias[i] : nullptr;

@@ -501,3 +501,26 @@ def test_wide_layer_of_few_examples_takes_narrow_chunks(L, dt, ks, Bn):
     assert nc >= 19
     want = (Bn * nc * 4 + 255) // 256 * 256
     assert L.dp_ghost_norm_linear_workspace(one, 1, Bn, 32, dt) == want
+
+
+@pytest.mark.parametrize("dt,T,Bn", [(D.DP_F32, 160, 1), (D.DP_F32, 300, 4), (D.DP_BF16, 300, 1),
+                                     (D.DP_BF16, 256, 12), (D.DP_BF16, 128, 4)])
+def test_launches_of_few_items_stay_within_one_round(L, dt, T, Bn):
+    """Layers with biases (which keep G as the chunked side) in a Gram launch that does not
+    occupy every workgroup slot: chunks are narrowed only as far as the items still run in
+    one round of the 256 compute units (two workgroups each at T <= 128)."""
+    shapes = [(768, 2304), (768, 768), (768, 3072), (3072, 768)] * 3
+    arr = (D.dp_linear_t * len(shapes))(*[_lin(d_in=a, lda=a, d_out=b, ldg=b, algo=D.DP_NORM_GRAM)
+                                          for a, b in shapes])
+    bias = (ctypes.c_void_p * len(shapes))(*[1 << 40] * len(shapes))
+    slots = 512 if T <= 128 else 256
+    pairs = 1 if dt == D.DP_BF16 and T <= 256 else (-(-T // 128)) * (-(-T // 128) + 1) // 2
+    whole = Bn * pairs * len(shapes)
+    ws = L.dp_ghost_norm_linear_bias_workspace(arr, bias, len(shapes), Bn, T, dt)
+    if not (dt == D.DP_BF16 and T <= 256):   # the biases take the vector kernel's partials too
+        lanes = 64 * (8 if dt == D.DP_BF16 else 4)
+        ws -= (Bn * sum(-(-b // lanes) for _, b in shapes) * 4 + 255) // 256 * 256
+    items = ws // 4                          # partials, rounded up to 64
+    if whole < slots:
+        assert items <= slots
+    assert items >= whole
