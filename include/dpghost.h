@@ -308,10 +308,10 @@ dp_status_t dp_clipped_grad_sum_grouped(const dp_linear_t* layers, float* const*
 /* The same with a caller-owned, 16-byte aligned workspace of at least
  * dp_clipped_grad_sum_split_workspace(...) bytes (a NULL workspace of 0 bytes gives
  * the call above). Where a launch's last round of 256 x 256 output tiles would
- * keep at most half of the compute units busy, each of its tiles is computed as
- * 2-8 consecutive K ranges on separate compute units; the fp32 partial tiles go
- * to the workspace and are added in order, so results differ from the call
- * above by fp32 rounding only. */
+ * keep at most half of the compute units busy, and long sums make it pay, each of
+ * its tiles is computed as 2-8 consecutive K ranges on separate compute units; the
+ * fp32 partial tiles go to the workspace and are added in order, so results differ
+ * from the call above by fp32 rounding only. (The size covers the noised form below too.) */
 size_t dp_clipped_grad_sum_split_workspace(const dp_linear_t* layers, int n_layers, int B, int T,
                                            dp_dtype_t dt, int transpose_out);
 dp_status_t dp_clipped_grad_sum_grouped_ws(const dp_linear_t* layers, float* const* outs,
@@ -348,7 +348,7 @@ dp_status_t dp_clipped_grad_sum_noised_grouped(const dp_linear_t* layers, float*
 /* The same with a caller-owned workspace of at least
  * dp_clipped_grad_sum_noised_grouped_workspace(...) bytes (a NULL workspace
  * of 0 bytes gives the call above). Where a launch's last round of 256 x 256
- * output tiles would keep at most half of the compute units busy (bf16,
+ * output tiles would keep at most half of the compute units busy, and long sums make it pay (bf16,
  * 16-byte rows, T a multiple of 32; for every other form too with the
  * dp_clipped_grad_sum_split_workspace(...) bytes), each of its tiles is computed as 2-8
  * consecutive K ranges on separate compute units; the fp32 partial tiles go

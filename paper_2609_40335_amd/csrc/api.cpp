@@ -404,9 +404,9 @@ std::vector<std::pair<bool, std::vector<const GemmEntry*>>> gemm_launches(
 }
 
 // Bytes of partial tiles the split tail of a clipped-sum plan needs (the
-// largest over its launches, which run one after another). every: for every
-// form of operand, or only those that could be split first (bf16, 16-byte rows,
-// whole 32-row stages), whose workspace query keeps its value.
+// largest over its launches, which run one after another). every: with noise or without,
+// for every form of operand; else with noise, and only the form that could be split
+// first (bf16, 16-byte rows, whole 32-row stages), which that workspace query answers for.
 size_t sum_split_bytes(const std::vector<GemmEntry>& entries, int B, int T, dp_dtype_t dt,
                        bool every) {
   size_t need = 0;
@@ -414,9 +414,13 @@ size_t sum_split_bytes(const std::vector<GemmEntry>& entries, int B, int T, dp_d
     if (!every && !dpg::dl_sum_applies(kdt(dt), vec, T, B)) continue;
     uint64_t tiles = 0;
     for (const GemmEntry* e : sel) tiles += (uint64_t)e->tm * e->tn;
-    const dpg::TailSplit t =
-        dpg::tail_split(tiles, dpg::sum_stages(kdt(dt), vec, T, B), device_cus());
-    need = std::max(need, (size_t)t.n_split * t.ks * dpg::SPLIT_TILE_BYTES);
+    const int form = dpg::sum_form(kdt(dt), vec, T, B);
+    for (const bool noised : {true, false}) {
+      if (!noised && !every) continue;
+      const dpg::TailSplit t = dpg::tail_split(tiles, dpg::sum_stages(form, T, B), form, noised,
+                                               device_cus());
+      need = std::max(need, (size_t)t.n_split * t.ks * dpg::SPLIT_TILE_BYTES);
+    }
   }
   return need;
 }

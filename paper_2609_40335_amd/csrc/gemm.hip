@@ -1458,7 +1458,8 @@ static hipError_t launch_kt(const GemmArgs& a0, int dt, bool vec, int cus, size_
   if (MODE == MODE_SUM && a.store) return hipErrorInvalidValue;
   uint32_t grid = a.n_items;
   if (MODE == MODE_SUM && a.part != nullptr && ((uintptr_t)a.part & 15) == 0) {
-    const TailSplit t = tail_split(a.n_items, sum_stages(dt, vec, a.T, a.B), cus);
+    const int form = sum_form(dt, vec, a.T, a.B);
+    const TailSplit t = tail_split(a.n_items, sum_stages(form, a.T, a.B), form, a.noise != 0, cus);
     if (t.n_split > 0 && (size_t)t.n_split * t.ks * SPLIT_TILE_BYTES <= part_bytes) {
       a.n_full = t.n_full;
       a.n_split = t.n_split;
@@ -1468,7 +1469,7 @@ static hipError_t launch_kt(const GemmArgs& a0, int dt, bool vec, int cus, size_
   }
   if (dt == DT_BF16) {
     const int form = a.big ? (int)FORM_BIG
-                           : (MODE == MODE_NORM ? norm_form(vec, a.T) : sum_form(vec, a.T, a.B));
+                           : (MODE == MODE_NORM ? norm_form(vec, a.T) : sum_form(dt, vec, a.T, a.B));
     launch_dl<MODE>(a, form, grid, s);
   } else {
     hipLaunchKernelGGL((split_gemm_kernel<MODE>), dim3(grid), dim3(GM_THREADS), 0, s, a);

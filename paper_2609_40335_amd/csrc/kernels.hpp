@@ -170,11 +170,13 @@ static_assert(sizeof(GemmArgs) <= 4096, "kernel arguments must stay within 4 KiB
 //          layers 768 -> 3072, 3072 tokens, us: T = 21: 217 SCALED, 353 RAGGED; 404 ROWS,
 //          592 STAGED (unaligned); T = 22: 217, 337; 404, 565; T = 42: 217, 271; 404,
 //          489; T = 43: 217, 255; 404, 477.
-enum GemmForm { FORM_PLAIN = 0, FORM_BIG, FORM_RAGGED, FORM_STAGED, FORM_ROWS, FORM_SCALED };
+//  FP32:   the fp32 kernel (split_gemm_kernel).
+enum GemmForm { FORM_PLAIN = 0, FORM_BIG, FORM_RAGGED, FORM_STAGED, FORM_ROWS, FORM_SCALED, FORM_FP32 };
 constexpr int DL_SUM_BK = 32;
 constexpr int DL_SUM_MAXB = 4096;  // clip factors held in LDS
 constexpr int ROWS_NUM = 3, ROWS_DEN = 2;
-inline int sum_form(bool vec, int T, int B) {
+inline int sum_form(int dt, bool vec, int T, int B) {
+  if (dt != DT_BF16) return FORM_FP32;
   if (T % DL_SUM_BK == 0) return !vec ? FORM_STAGED : B <= DL_SUM_MAXB ? FORM_PLAIN : FORM_RAGGED;
   const int64_t padded = (int64_t)((T + DL_SUM_BK - 1) / DL_SUM_BK) * DL_SUM_BK;
   if (padded * ROWS_DEN > (int64_t)T * ROWS_NUM) return vec ? FORM_SCALED : FORM_ROWS;
@@ -190,37 +192,53 @@ inline bool dl_sum_applies(int dt, bool vec, int T, int B) {
 
 constexpr int SP_BK = 16;          // K rows per stage of the fp32 kernel
 // K stages of a clipped sum's launch.
-inline int sum_stages(int dt, bool vec, int T, int B) {
+inline int sum_stages(int form, int T, int B) {
   const int64_t K = (int64_t)B * T;
-  if (dt != DT_BF16) return (int)((K + SP_BK - 1) / SP_BK);
-  const int form = sum_form(vec, T, B);
+  if (form == FORM_FP32) return (int)((K + SP_BK - 1) / SP_BK);
   if (form == FORM_ROWS || form == FORM_SCALED) return (int)((K + DL_SUM_BK - 1) / DL_SUM_BK);
   return (int)((int64_t)B * ((T + DL_SUM_BK - 1) / DL_SUM_BK));
 }
 
 // The last round of a launch of n_tiles equal tiles on `cus` CUs holds
 // r = n_tiles mod cus of them (all of them if n_tiles < cus). When r is at most
-// half the CUs, each of those tiles is split into ks consecutive K ranges of at
-// least 4 stages (ks <= 8, r * ks <= cus), so the round takes about 1/ks of a
-// tile's time. All forms of the sum are split alike: one 768 -> 3072 layer at
-// B = 24, T = 128 is 36 tiles (norm and sum: 84 us whole, 62 us split); the fp32
-// sums of DistilGPT2 there, 1239 tiles in two launches, took 2551 and take 2383 us.
+// half the CUs, each of those tiles may be split into ks consecutive K ranges of at
+// least 4 stages (ks <= 8, r * ks <= cus). The round then takes about 1/ks of a
+// tile's time, plus the fix-up launch (SPLIT_US) and the partial tiles' way to memory and
+// back (SPLIT_PART_US each: 512 KB at about 6 TB/s); where noise is drawn, the fix-up
+// spreads that over the chip too, which takes a whole tile SPLIT_NOISE_US. The ks of the
+// shortest sum is taken, 1 where nothing is gained. Measured, whole and split: plain sums of
+// one 768 -> 3072 layer at K = 3072 (36 tiles) 73 and 43 us; of four layers 768 -> 2304,
+// 768, 3072 and 3072 -> 768 at K = 256 (108 tiles) 14 and 32, with noise 29 and 38; of one tile
+// at K = 256 with noise 30 and 17.
+constexpr double SPLIT_US = 3.0, SPLIT_PART_US = 0.0875, SPLIT_NOISE_US = 13.0;
+// Time of one K stage of a tile (us) on a chip with few tiles, by the form of the sum.
+inline double stage_us(int form) {
+  switch (form) {
+    case FORM_PLAIN: return 0.66;
+    case FORM_SCALED: return 0.8;
+    case FORM_RAGGED: return 1.1;
+    case FORM_FP32: return 1.6;
+    default: return 1.9;
+  }
+}
 struct TailSplit {
   uint32_t n_full, n_split;
   int32_t ks;
 };
-inline TailSplit tail_split(uint64_t n_tiles, int k_stages, int cus) {
+inline TailSplit tail_split(uint64_t n_tiles, int k_stages, int form, bool noised, int cus) {
   TailSplit t{(uint32_t)n_tiles, 0u, 1};
   if (cus <= 0 || n_tiles == 0) return t;
   const uint64_t r = n_tiles % (uint64_t)cus;
   if (r == 0 || 2 * r > (uint64_t)cus) return t;
-  int ks = (int)((uint64_t)cus / r);
-  ks = ks < 8 ? ks : 8;
-  ks = ks < k_stages / 4 ? ks : k_stages / 4;
-  if (ks < 2) return t;
+  const int top = (int)((uint64_t)cus / r);
+  double best = k_stages * stage_us(form) + (noised ? SPLIT_NOISE_US : 0.0);
+  for (int ks = 2; ks <= 8 && ks <= top && ks <= k_stages / 4; ++ks) {
+    const double us = (k_stages + ks - 1) / ks * stage_us(form) + SPLIT_US + (double)r * ks * SPLIT_PART_US;
+    if (us < best) { best = us; t.ks = ks; }
+  }
+  if (t.ks == 1) return t;
   t.n_full = (uint32_t)(n_tiles - r);
   t.n_split = (uint32_t)r;
-  t.ks = ks;
   return t;
 }
 constexpr size_t SPLIT_TILE_BYTES = (size_t)GM_BM * GM_BN * 4;  // one fp32 partial tile

@@ -373,3 +373,29 @@ def test_linear_form_leaves_its_workspace_alone():
     assert bool((ws == 0xAB).all())
     want = (per_example(A, G) * c.double().view(B, 1, 1)).sum(0)
     assert float((out.double() - want).norm() / want.norm()) < 1e-5
+
+
+@pytest.mark.parametrize("B,T,shapes,split", [
+    (1, 256, [(768, 2304), (768, 768), (768, 3072), (3072, 768)], False),   # 108 tiles of 8 stages
+    (10, 24, [(768, 2304), (768, 768), (768, 3072), (3072, 768)], False),   # short examples
+    (24, 128, [(768, 3072)], True),                                         # 36 tiles of 96
+], ids=["short-sums", "short-examples", "long-sums"])
+def test_sums_are_split_only_where_that_pays(B, T, shapes, split):
+    """Partial tiles cost their way to memory and back, so many tiles of short sums write
+    none, whatever workspace they are given; few tiles of long sums do."""
+    import ctypes
+    from paper_2609_40335_amd import dpghost as dp
+    L = dp.lib()
+    layers = [operands(8 + i, B, T, a, b, torch.bfloat16, a, b, 0)[:2] for i, (a, b) in enumerate(shapes)]
+    outs = [torch.zeros(a, b, device="cuda") for a, b in shapes]
+    descs = (dp.dp_linear_t * len(shapes))(*[dp._layer(*l) for l in layers])
+    ptrs = (ctypes.c_void_p * len(shapes))(*[o.data_ptr() for o in outs])
+    c = torch.ones(B, device="cuda")
+    ws = torch.full((256 * 256 * 256 * 4,), 0xAB, dtype=torch.uint8, device="cuda")
+    st = L.dp_clipped_grad_sum_grouped_ws(descs, ptrs, len(shapes), c.data_ptr(), B, T, dp.DP_BF16, 0,
+                                          0, ws.data_ptr(), ws.numel(), dp._stream(None))
+    assert st == 0
+    assert bool((ws == 0xAB).all()) != split
+    for (A, G), o in zip(layers, outs):
+        want = per_example(A, G).sum(0)
+        assert float((o.double() - want).norm() / want.norm()) < 1e-5
