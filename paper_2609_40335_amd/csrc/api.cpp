@@ -202,7 +202,7 @@ int pick_chunks(int64_t width, int ks, int64_t items_per_chunk, int64_t other, i
 // item's stages are a serial chain (about 0.5 us each), so such a launch takes
 // as long as its longest item. Narrower chunks shorten it and fill idle
 // compute units, and each one repeats the layer's A stages. The choice is the shortest
-// longest item among the widths whose items still run in one round, the widest on a
+// longest item among the widths whose items still run in one round, the narrowest on a
 // tie; nothing is gained below the length of the other layers' items (other_len).
 // (d_in = 768, d_out = 3072, B = 24, T = 128: the norm took 34 us of 109 for norm and
 // sum, 12 of 87 with it.) A launch of more than one round keeps its items: each
@@ -231,7 +231,10 @@ int few_items_chunk(const std::vector<GramShape>& v, int64_t other, int64_t othe
       longest = std::max(longest, g.nx + std::min<int64_t>(q, g.ny) + GRAM_FILL);
       total += g.items * ceil_div(g.ny, q);
     }
-    if (total <= slots && (best == 0 || longest <= best_len)) { best = q; best_len = longest; }
+    if (total <= slots && (best == 0 || longest < best_len || longest == other_len)) {
+      best = q;
+      best_len = longest;
+    }
   }
   if (best == 0 && std::any_of(v.begin(), v.end(), [&](const GramShape& g) { return g.ny > wide; }))
     best = 64;
@@ -279,9 +282,15 @@ NormPlan plan_norm(const dp_linear_t* layers, int n, int B, int T, dp_dtype_t dt
     wide_items[vec] += per_chunk * ceil_div(L.d_out, width[i]);
     wide_len[vec] = std::max(wide_len[vec], ceil_div(L.d_in, ks) + width[i] / ks + GRAM_FILL);
   }
-  int few[2];  // stages per G chunk where a launch is short of items, else 0
-  for (int v = 0; v < 2; ++v)
-    few[v] = lean ? 0 : few_items_chunk(shapes[v], wide_items[v], wide_len[v], slots, KG_SPLIT / ks);
+  // Stages per G chunk where a launch is short of items, else 0. Two workgroups of bf16 rows without
+  // 16-byte alignment share a compute unit at any T and hide each other's loads (four layers
+  // 768 -> 2304 and so on at B = 19, T = 160: 84 us cut to one workgroup per unit, 58 to
+  // two); fp32 pairs of T-tiles fit twice too, but wait for the matrix core (335 and 462 us).
+  int few[2];
+  for (int v = 0; v < 2; ++v) {
+    const int64_t room = T > dpg::GR_TM && v == 0 && dt == DP_BF16 ? 2 * slots : slots;
+    few[v] = lean ? 0 : few_items_chunk(shapes[v], wide_items[v], wide_len[v], room, KG_SPLIT / ks);
+  }
   for (int i = 0; i < n; ++i) {
     const dp_linear_t& L = layers[i];
     float* const bg = bias ? bias[i] : nullptr;
