@@ -13,9 +13,8 @@
  *    example b at row b*T + t. bf16 data is passed as its 16-bit patterns.
  *  - A matrix given with row stride ld > its width occupies ld elements in
  *    every row, the last one included (as a [rows, ld] buffer viewed to
- *    fewer columns does). When its rows are 16-byte aligned and ld is a
- *    whole number of 16-byte chunks, kernels may read, but never use, the
- *    elements between the width and the next 16-byte boundary of a row.
+ *    fewer columns does). Kernels may read, but never use, a row's elements
+ *    between its width and ld.
  *  - Outputs are fp32. Squared norms add across calls ("accumulate" = 1
  *    means +=, 0 means overwrite), which is eq. 6 / eq. 10.
  *  - `stream` is a hipStream_t (NULL = the default stream). Calls are
@@ -157,12 +156,13 @@ dp_status_t dp_ghost_norm_linear_bias_grouped(const dp_linear_t* layers, float* 
  * operation as dp_ghost_norm_linear_bias_grouped, bit for bit, with the
  * partial sums in a static device scratch of DP_NOALLOC_SCRATCH_BYTES that
  * the library holds on each device from its load to the end of the process,
- * instead of a caller's workspace. It calls no allocating routine; the first
+ * instead of a caller's workspace. (Where the workspace form would cut a launch of few
+ * items into more partials than the scratch holds, this one keeps fewer, longer
+ * ones, and the two agree up to fp32 summation order.) It calls no allocating routine; the first
  * call on a device looks up that device's scratch address
- * (hipGetSymbolAddress) once. A call whose partials need more than the
- * scratch holds (dp_ghost_norm_linear_bias_workspace(...) bytes, so
- * B * (partials per example) * 4 rounded up) returns DP_EUNSUPPORTED before
- * any launch. Every call on one device shares that device's scratch: calls
+ * (hipGetSymbolAddress) once. A call whose partials (B * (partials per
+ * example) * 4 bytes rounded up) do not fit the scratch even so returns
+ * DP_EUNSUPPORTED before any launch. Every call on one device shares that device's scratch: calls
  * that overlap on one device (other streams, other threads) race and must be
  * ordered by the caller; nothing in the scratch needs to start at zero (every
  * partial is written before it is read). */

@@ -269,7 +269,7 @@ __device__ __forceinline__ void stage_mfma_split(const u32x4* __restrict__ lds,
 // Otherwise: 16-byte global loads of any alignment. Rows past T repeat row
 // T-1 and are zeroed on their way to LDS; the stage that holds the last column
 // reads its last chunk element by element. (The norms of GPT-2 at B = 24, T = 100
-// with a V = 50257 head took 516 us with one load per element; 232 us with this.)
+// with a V = 50257 head took 517 us with one load per element; 202 us with this.)
 template <int DT, bool VEC>
 struct TileStream {
   static constexpr int EPC = (DT == DT_BF16) ? 8 : 4;
@@ -352,7 +352,9 @@ template <int PAT> struct PatRows { static constexpr int ROWS = PAT == PAT_OFF ?
 
 // fp32 examples of one T-tile multiply on the bf16 matrix cores (split_f32): the
 // fp32 MFMAs bounded them (norms of DistilGPT2 at B = 24, T = 128, V = 50257
-// unpadded: 780 us, 496 with it; error against fp64 8.4e-8, 2.7e-8 with it). Pairs of
+// unpadded: 968 us, 512 with it; error against fp64 9e-8, 3e-8 with it, and 0.3 to 1.3 of
+// the fp32 MFMAs' over operands of one sign and both, T = 1 to 128, where both are a
+// rounding or two). Pairs of
 // T-tiles keep the fp32 MFMAs: the 256-row stages' planes and the partial sums
 // spilled registers and were up to 15 % slower (B = 8, T = 300, V = 50257).
 template <int DT, int PF>
