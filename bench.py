@@ -47,8 +47,8 @@ PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X dense fp32 matrix
 # HBM bytes per launch of the clipped-sum kernel: rocprofv3 FETCH_SIZE x 2 +
 # WRITE_SIZE x 1 (factors from a plain 1 GiB copy), recorded for the kernel
 # source with this SHA-256; any other source reports null.
-GEMM_TRAFFIC = {"gemm.hip sha256": "860886f34ee4ab704e76273f9181c1c00763de78e3d50e729ec42bb66e3afcfc",
-                "bytes": 2697737984}
+GEMM_TRAFFIC = {"gemm.hip sha256": "1549f4c7fea45b6cad193d5620c17b8f34cdbcb87e10925d4d72661d638d5803",
+                "bytes": 2699441408}
 
 
 def log(*a):

@@ -205,11 +205,11 @@ inline int sum_stages(int form, int T, int B) {
 // least 4 stages (ks <= 8, r * ks <= cus). The round then takes about 1/ks of a
 // tile's time, plus the fix-up launch (SPLIT_US) and the partial tiles' way to memory and
 // back (SPLIT_PART_US each: 512 KB at about 6 TB/s); where noise is drawn, the fix-up
-// spreads that over the chip too, which takes a whole tile SPLIT_NOISE_US. The ks of the
-// shortest sum is taken, 1 where nothing is gained. Measured, whole and split: plain sums of
-// one 768 -> 3072 layer at K = 3072 (36 tiles) 73 and 43 us; of four layers 768 -> 2304,
-// 768, 3072 and 3072 -> 768 at K = 256 (108 tiles) 14 and 32, with noise 29 and 38; of one tile
-// at K = 256 with noise 30 and 17.
+// spreads that over the chip too, which takes a whole tile SPLIT_NOISE_US. The largest ks
+// that gains by this is taken (shorter ranges round less), 1 where none does. Measured, whole
+// and split: norm and plain sum of one 768 -> 3072 layer at K = 3072 (36 tiles) 84 and 62 us; plain
+// sums of four layers 768 -> 2304, 768, 3072 and 3072 -> 768 at K = 256 (108 tiles) 14 and 32,
+// with noise 29 and 38; of one tile at K = 256 with noise 30 and 17.
 constexpr double SPLIT_US = 3.0, SPLIT_PART_US = 0.0875, SPLIT_NOISE_US = 13.0;
 // Time of one K stage of a tile (us) on a chip with few tiles, by the form of the sum.
 inline double stage_us(int form) {
@@ -217,7 +217,7 @@ inline double stage_us(int form) {
     case FORM_PLAIN: return 0.66;
     case FORM_SCALED: return 0.8;
     case FORM_RAGGED: return 1.1;
-    case FORM_FP32: return 1.6;
+    case FORM_FP32: return 2.4;
     default: return 1.9;
   }
 }
@@ -231,12 +231,15 @@ inline TailSplit tail_split(uint64_t n_tiles, int k_stages, int form, bool noise
   const uint64_t r = n_tiles % (uint64_t)cus;
   if (r == 0 || 2 * r > (uint64_t)cus) return t;
   const int top = (int)((uint64_t)cus / r);
-  double best = k_stages * stage_us(form) + (noised ? SPLIT_NOISE_US : 0.0);
-  for (int ks = 2; ks <= 8 && ks <= top && ks <= k_stages / 4; ++ks) {
-    const double us = (k_stages + ks - 1) / ks * stage_us(form) + SPLIT_US + (double)r * ks * SPLIT_PART_US;
-    if (us < best) { best = us; t.ks = ks; }
-  }
-  if (t.ks == 1) return t;
+  int ks = top < 8 ? top : 8;
+  ks = ks < k_stages / 4 ? ks : k_stages / 4;
+  const double whole = k_stages * stage_us(form) + (noised ? SPLIT_NOISE_US : 0.0);
+  auto gains = [&](int n) {
+    return (k_stages + n - 1) / n * stage_us(form) + SPLIT_US + (double)r * n * SPLIT_PART_US < whole;
+  };
+  while (ks >= 2 && !gains(ks)) --ks;
+  if (ks < 2) return t;
+  t.ks = ks;
   t.n_full = (uint32_t)(n_tiles - r);
   t.n_split = (uint32_t)r;
   return t;
