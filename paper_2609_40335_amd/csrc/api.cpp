@@ -204,6 +204,7 @@ int pick_chunks(int64_t width, int ks, int64_t items_per_chunk, int64_t other, i
 // compute units, and each one repeats the layer's A stages. The choice is the shortest
 // longest item among the widths whose items still run in one round, the narrowest on a
 // tie; nothing is gained below the length of the other layers' items (other_len).
+// room: the slots taken where nothing can be shortened within `slots`.
 // (d_in = 768, d_out = 3072, B = 24, T = 128: the norm took 34 us of 109 for norm and
 // sum, 12 of 87 with it.) A launch of more than one round keeps its items: each
 // chunk's repeated A stages cost more than the shorter tail gains, and as
@@ -219,22 +220,32 @@ struct GramShape {
   int64_t items, nx, ny;  // items per chunk; stages of A, of G
 };
 int few_items_chunk(const std::vector<GramShape>& v, int64_t other, int64_t other_len,
-                    int64_t slots, int64_t wide) {
-  int64_t items = other;
-  for (const GramShape& g : v) items += g.items;
+                    int64_t slots, int64_t room, int64_t wide) {
+  int64_t items = other, whole = other_len;
+  for (const GramShape& g : v) {
+    items += g.items;
+    whole = std::max(whole, g.nx + g.ny + GRAM_FILL);
+  }
   if (v.empty() || items >= slots) return 0;
   int best = 0;
-  int64_t best_len = 0;
-  for (int q : {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
-    int64_t longest = other_len, total = other;
-    for (const GramShape& g : v) {
-      longest = std::max(longest, g.nx + std::min<int64_t>(q, g.ny) + GRAM_FILL);
-      total += g.items * ceil_div(g.ny, q);
+  int64_t best_len = whole;
+  auto choose = [&](int64_t limit) {
+    for (int q : {2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
+      int64_t longest = other_len, total = other;
+      for (const GramShape& g : v) {
+        longest = std::max(longest, g.nx + std::min<int64_t>(q, g.ny) + GRAM_FILL);
+        total += g.items * ceil_div(g.ny, q);
+      }
+      if (total <= limit && (best == 0 || longest < best_len || longest == other_len)) {
+        best = q;
+        best_len = longest;
+      }
     }
-    if (total <= slots && (best == 0 || longest < best_len || longest == other_len)) {
-      best = q;
-      best_len = longest;
-    }
+  };
+  choose(slots);
+  if (best_len == whole && room > slots) {  // nothing is shortened
+    best = 0;
+    choose(room);
   }
   if (best == 0 && std::any_of(v.begin(), v.end(), [&](const GramShape& g) { return g.ny > wide; }))
     best = 64;
@@ -283,13 +294,15 @@ NormPlan plan_norm(const dp_linear_t* layers, int n, int B, int T, dp_dtype_t dt
     wide_len[vec] = std::max(wide_len[vec], ceil_div(L.d_in, ks) + width[i] / ks + GRAM_FILL);
   }
   // Stages per G chunk where a launch is short of items, else 0. Two workgroups of bf16 rows without
-  // 16-byte alignment share a compute unit at any T and hide each other's loads (four layers
-  // 768 -> 2304 and so on at B = 19, T = 160: 84 us cut to one workgroup per unit, 58 to
-  // two); fp32 pairs of T-tiles fit twice too, but wait for the matrix core (335 and 462 us).
+  // 16-byte alignment share a compute unit at any T and hide each other's loads, so where one round of
+  // one per unit leaves no room to shorten the longest item, a round of two is taken (four layers
+  // 768 -> 2304 and so on at B = 19, T = 160: 84 us and 58; with room at B = 1: 26 us in one, 32 in
+  // two). fp32 pairs of T-tiles fit twice too, but wait for the matrix core (335 and 462 us).
   int few[2];
   for (int v = 0; v < 2; ++v) {
     const int64_t room = T > dpg::GR_TM && v == 0 && dt == DP_BF16 ? 2 * slots : slots;
-    few[v] = lean ? 0 : few_items_chunk(shapes[v], wide_items[v], wide_len[v], room, KG_SPLIT / ks);
+    few[v] = lean ? 0 : few_items_chunk(shapes[v], wide_items[v], wide_len[v], slots, room,
+                                         KG_SPLIT / ks);
   }
   for (int i = 0; i < n; ++i) {
     const dp_linear_t& L = layers[i];
